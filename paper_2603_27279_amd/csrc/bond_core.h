@@ -70,7 +70,9 @@ __device__ __forceinline__ void bond_one(V3<H> x1, V3<H> x2, Q4<H> q1, Q4<H> q2,
     // radial: + g_r (v2 - v1) . r_f-hat, the relative velocity seen from C;
     // shear: K_s gamma becomes K_s gamma + g_s gamma-dot (no term where s-hat is
     // undefined, sigma = 0)
-    const H frad = H(Kr) * dr + H(dm->gr) * dot(qrot_inv(qc, V3<H>{dm->dv.x, dm->dv.y, dm->dv.z}), rhat);
+    // (the contraction is spelled out so that every kernel rounds alike)
+    const V3<H> vc = qrot_inv(qc, V3<H>{dm->dv.x, dm->dv.y, dm->dv.z});
+    const H frad = __builtin_fma(dm->gr, dot(vc, rhat), Kr * dr);
     R ks = R(Ks) * g;
     if (dm->rates && sigma > R(0))
       ks = ks + R(dm->gs) * (R)(((double)gamma - dm->hprev[0]) * dm->idt) / sigma;

@@ -7,6 +7,7 @@
 #include "lbm.h"
 #include "lbm_internal.h"
 #include "rod_adjoint.h"
+#include "step_internal.h"
 
 #include <algorithm>
 #include <cmath>
@@ -63,6 +64,11 @@ struct rod_ctx {
   int adj_nwork = 0;
   std::vector<void*> plan_allocs;   // dipole work list, slot counts, partial slots
   std::vector<int> mrange_h;        // [2M] member particle ranges
+  int max_member = 0;               // particles of the largest member
+  // Second set of state planes (x, v, q, w as in a recorded state, then moments)
+  // of the fused steps of small systems, or null.
+  double* alt = nullptr;
+  float* alt_muf = nullptr;
   int plan_small = -1, plan_target = 1024;  // current dipole layout
   std::vector<int> mslots_h;        // [M] source ranges per member of the current layout
   std::vector<int> mlen_h;          // [M] length of those ranges
@@ -433,6 +439,13 @@ static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
   c->mslots_h = mslots;
   c->mlen_h = mlen;
   c->d.dip_small = small ? 1 : 0;
+  c->max_member = max_member;
+  c->alt = nullptr;
+  c->alt_muf = nullptr;
+  if (small && c->d.dcut == 0.0 && !c->d.ew_on) {
+    TRY(palloc(c, &c->alt, 16 * (size_t)N));
+    if (c->d.muf) TRY(palloc(c, &c->alt_muf, 3 * (size_t)N));
+  }
   c->plan_small = spatial ? 2 : small ? 1 : 0;
   c->d.dperm = nullptr;
   c->d.sbox = nullptr;
@@ -635,7 +648,7 @@ static size_t workspace_bytes(const rod_desc* d, int max_slots) {
   size_t N = d->n_particles, R = d->n_rods, M = d->n_members;
   size_t cells = d->contact_on ? next_pow2(std::max<size_t>(1024, 2 * N)) : 1;
   size_t b = 0;
-  b += N * (1 + 4 + 4 + 1) + 8 * N * 4 + 8 * N * 4 + 8 * R * 4 + 4 * M * 3;  // topology
+  b += N * (1 + 4 + 4 + 1) + 8 * N * 4 + 8 * N * 4 + 8 * R * 4 + 4 * M * 3 + 4 * (R + 1);  // topology
   b += 8 * 3 * N + 4 * 3 * N + 8 * 9 * N + 8 * 4 * N;                         // mu, bonds
   b += 8 * (size_t)max_slots * 6 * N + 8 * 4 * N;                               // dipole, contact
   if (d->precision == ROD_MIXED && d->dipole_on) b += 4 * (size_t)max_slots * 6 * N;  // FP32 slots
@@ -661,6 +674,16 @@ static size_t workspace_bytes(const rod_desc* d, int max_slots) {
   if (d->dipole_on) b += 4 * N + 48 * ((N + 63) / 64);  // spatial order and its chunk boxes
   if (d->bond_damping) b += 8 * 4 * R + 8 * 2 * 5 * N;                       // bond damping
   b += 8 * 18 * N + 8 * 9 * M;                                                  // energy
+  if (!dcut && !(d->box[0] > 0)) {  // second state planes of the fused small steps
+    std::vector<long> size(M, 0);
+    long largest = 0;
+    for (size_t r = 0; r < R; ++r) {
+      long& m = size[d->rod_member[r]];
+      m += d->rod_offset[r + 1] - d->rod_offset[r];
+      largest = std::max(largest, m);
+    }
+    if (largest <= 2048) b += (8 * 16 + (d->precision == ROD_MIXED ? 12 : 0)) * N;
+  }
   return b;
 }
 
@@ -717,8 +740,62 @@ struct NoRecord {
 // further step, and post; the fused kick ends one step and starts the next, and
 // the level counter it reads alternates between step[1] and step[2]. Other
 // modes: pre, forces, post per step.
+// Whether rod_step takes the fused steps of small systems (k_step.hip): batched
+// launches of the small-member layout without a dipole cutoff, a box or contact
+// lists. A timed run takes the two-launch chain, whose kernels have classes of
+// their own; states are the same bits.
+static bool small_steps(const rod_ctx* c) {
+  return c->launch_mode == ROD_LAUNCH_BATCHED && !c->timing && c->alt && !c->d.use_lists &&
+         !c->d.ibm_u;
+}
+// Whether a launch serves many steps (a workgroup per member). Its level is an
+// argument, so it is never part of a captured graph.
+static bool many_steps(const rod_ctx* c) {
+  return small_steps(c) && !c->d.hm && c->max_member <= STEPS_MAX;
+}
+
+// n steps of a small system from level lvl, a launch per STEPS_LAUNCH of them (a
+// few milliseconds each).
+constexpr int STEPS_LAUNCH = 1000;
+static int enqueue_many(rod_ctx* c, int64_t n, int64_t lvl) {
+  for (int64_t k = 0; k < n; k += STEPS_LAUNCH)
+    HIPC(launch_steps(c->d, c->desc.precision, c->max_member, lvl + k, (int)std::min<int64_t>(STEPS_LAUNCH, n - k),
+                      c->s));
+  return ROD_OK;
+}
+
+// n fused steps, one launch each after the opening pre. The state alternates
+// between the caller's planes and c->alt, so that the last step reads c->alt and
+// leaves the result with the caller.
+static int enqueue_small(rod_ctx* c, int64_t n) {
+  const long N = c->d.n;
+  struct Set { double *x, *v, *q, *w, *mu; float* muf; };
+  const Set sets[2] = {{c->d.x, c->d.v, c->d.q, c->d.w, c->d.mu, c->d.muf},
+                       {c->alt, c->alt + 3 * N, c->alt + 6 * N, c->alt + 10 * N, c->alt + 13 * N,
+                        c->alt_muf}};
+  int at = n & 1 ? 1 : 0;  // planes of the first level evaluated
+  Dev d = c->d;
+  d.lazy_cells = 1;  // nothing searches the cell list
+  d.far_ok = 0;      // nor reads the chunk boxes
+  d.mu = sets[at].mu;
+  d.muf = sets[at].muf;
+  if (at) d.nx = c->alt;
+  HIPC(launch_pre(d, PRE_STEP, c->s));
+  d.nx = nullptr;
+  for (int64_t k = 1; k <= n; ++k, at = 1 - at) {
+    const Set& from = sets[at];
+    const Set& to = sets[1 - at];
+    d.x = from.x; d.v = from.v; d.q = from.q; d.w = from.w; d.mu = from.mu; d.muf = from.muf;
+    const StepOut o{to.x, to.v, to.q, to.w, to.mu, to.muf, nullptr, k == n, 0};
+    HIPC(launch_step(d, c->desc.precision, o, c->s));
+    d.lc = 3 - d.lc;
+  }
+  return ROD_OK;
+}
+
 static int enqueue_steps(rod_ctx* c, int64_t n) {
   if (n <= 0) return ROD_OK;
+  if (small_steps(c)) return enqueue_small(c, n);
   // contact by candidate lists: the particle kernels of the stepping chain leave
   // the cell list empty, and the contact launch fills it when the lists are
   // rebuilt (the cell list serves nothing else between rebuilds)
@@ -979,15 +1056,17 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   d.i_lo = 0; d.i_hi = N;
   d.x = b->x; d.v = b->v; d.q = b->q; d.w = b->w; d.F = b->force; d.T = b->torque;
   d.mb = b->m_body; d.field = b->field; d.extF = b->ext_force; d.extT = b->ext_torque;
-  uint8_t* bflags; int *rod_d, *mem_d, *mrange_d; int8_t* bc_d;
+  uint8_t* bflags; int *rod_d, *rod_off_d, *mem_d, *mrange_d; int8_t* bc_d;
   double *minv_d, *Iinv_d, *mass_d, *inertia_d, *bref_d, *rodK_d;
   if ((rc = dalloc(c, &bflags, N)) || (rc = dalloc(c, &rod_d, N)) || (rc = dalloc(c, &mem_d, N)) ||
+      (rc = dalloc(c, &rod_off_d, (size_t)R + 1)) ||
       (rc = dalloc(c, &bc_d, N)) || (rc = dalloc(c, &minv_d, N)) || (rc = dalloc(c, &Iinv_d, N)) ||
       (rc = dalloc(c, &mass_d, N)) || (rc = dalloc(c, &inertia_d, N)) ||
       (rc = dalloc(c, &bref_d, 4 * (size_t)N)) || (rc = dalloc(c, &rodK_d, 4 * (size_t)R)) ||
       (rc = dalloc(c, &mrange_d, 2 * (size_t)M)))
     return cleanup(rc);
   struct Up { void* dst; const void* src; size_t bytes; } ups[] = {
+      {rod_off_d, c->rod_offset.data(), 4 * ((size_t)R + 1)},
       {bflags, bfl.data(), (size_t)N}, {rod_d, rod.data(), 4 * (size_t)N},
       {mem_d, mem.data(), 4 * (size_t)N}, {bc_d, bc.data(), (size_t)N},
       {minv_d, minv.data(), 8 * (size_t)N}, {Iinv_d, Iinv.data(), 8 * (size_t)N},
@@ -997,7 +1076,7 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   for (auto& u : ups)
     if (hipMemcpy(u.dst, u.src, u.bytes, hipMemcpyHostToDevice) != hipSuccess)
       return cleanup(fail(ROD_E_HIP, "upload failed"));
-  d.bflags = bflags; d.rod = rod_d; d.mem = mem_d; d.bc = bc_d;
+  d.bflags = bflags; d.rod = rod_d; d.rod_off = rod_off_d; d.mem = mem_d; d.bc = bc_d;
   d.minv = minv_d; d.Iinv = Iinv_d; d.mass = mass_d; d.inertia = inertia_d;
   d.bref = bref_d; d.rodK = rodK_d; d.mrange = mrange_d;
   float* muf = nullptr;
@@ -1159,7 +1238,11 @@ int rod_step(rod_ctx* c, int64_t n) {
     while (k < n) {
       const int64_t rel = c->h_step + k - c->tape.start_step;
       TRY(tape_before_step(c->tape, c->d, c->s, c->h_step + k));
-      if (!c->timing && rel % every == 0 && n - k >= every && rel + every <= c->tape.capacity) {
+      if (many_steps(c)) {  // up to the next checkpoint, within the tape's capacity
+        const int64_t m = std::min(std::min<int64_t>(every - rel % every, n - k), c->tape.capacity - rel);
+        TRY(enqueue_many(c, m, c->h_step + k));
+        k += m;
+      } else if (!c->timing && rel % every == 0 && n - k >= every && rel + every <= c->tape.capacity) {
         if (!c->tgexec) TRY(capture_steps(c, every, &c->tgexec));
         HIPC(hipGraphLaunch(c->tgexec, c->s));
         k += every;
@@ -1170,6 +1253,8 @@ int rod_step(rod_ctx* c, int64_t n) {
     }
   } else if (c->launch_mode == ROD_LAUNCH_PER_ROD) {
     for (int64_t k = 0; k < n; ++k) TRY(enqueue_step_per_rod(c));
+  } else if (many_steps(c)) {
+    TRY(enqueue_many(c, n, c->h_step));
   } else {
     int64_t left = n;
     if (!c->timing && c->desc.graph_steps > 0 && left >= c->desc.graph_steps) {

@@ -30,6 +30,7 @@ struct Dev {
   // topology and constants
   const uint8_t* bflags;   // bit0: bond (k, k+1); bit1: bond (k-1, k)
   const int* rod;          // rod of each particle
+  const int* rod_off;      // [R + 1] first particle of each rod
   const int* mem;          // member of each particle
   const int8_t* bc;        // boundary condition of each particle
   const double *minv, *Iinv, *mass, *inertia;
