@@ -301,7 +301,8 @@ int rod_grad(rod_ctx* c, const rod_cotangent* gy, rod_gradients* gx);
  * While enabled (enable != 0), rod_step launches every step eagerly (no graph)
  * and hands each kernel launch a pair of events that the runtime stamps with
  * that kernel's own start and end (hipExtLaunchKernel), so launch gaps are
- * not counted. rod_kernel_times synchronises, adds up the elapsed time of all
+ * not counted. Systems whose steps are single launches otherwise run the force
+ * and kick launches of larger ones, with the same results. rod_kernel_times synchronises, adds up the elapsed time of all
  * timed launches since the last read per kernel class and resets the sums:
  * ms[ROD_KERNEL_COUNT] (milliseconds) and launches[ROD_KERNEL_COUNT] (host
  * arrays, may be NULL). The library holds at most 4096 pending event pairs;
@@ -348,7 +349,9 @@ int rod_autotune(rod_ctx* c, const char* cache_path, int32_t force, char* report
  * 65536 particles (above, the candidate-list search is a launch of its own,
  * timed as ROD_KERNEL_CONTACT); between two consecutive steps of one call the
  * closing half-kick and the next step's opening half-kick, drift and rotation
- * share one launch.
+ * share one launch. In the small-member dipole layout a whole step is one
+ * launch, and members of at most 32 particles (without Hertz-Mindlin contact)
+ * take many steps per launch, whatever graph_steps says.
  * ROD_LAUNCH_SEPARATE: as batched, with the three force terms launched as
  * separate kernels and no kick fusion (per-term timing).
  * ROD_LAUNCH_PER_ROD: the plain per-rod loop, every kernel launched once per

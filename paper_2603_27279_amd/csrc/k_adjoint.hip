@@ -24,10 +24,12 @@
 //             = -dU/da), evaluated once with i as target and once as source;
 //   Zeeman, torque m x B, damping, contact, and m = R(q) m_body - by hand.
 #include "rod_adjoint.h"
+#include "small_body.h"  // (before dual.h, whose sqrt would hide the library's)
 #include "bond_core.h"
 #include "dual.h"
 #include "particle_body.h"
 #include "fixsum.h"
+#include "step_internal.h"
 
 #include <algorithm>
 
@@ -77,44 +79,65 @@ __device__ void richardson_vjp(Q4<double> q, V3<double> w, double dt, Q4<double>
 }
 
 // ---------------------------------------------------------------- local terms
-// Post-kick VJP and the per-particle force terms (Zeeman, dipole torque,
-// damping). S1 is the state of the level whose forces are reversed; S0 the
-// state one level earlier (ADJ_STEP only).
-__device__ __forceinline__ void adj_local(const Dev& d, const Adj& a, long i, const double* S0,
-                                          const double* S1, int koff, int mode) {
-  const long long lvl = *a.lbase + koff;
+// Cotangent of one particle's state.
+struct Cot {
+  V3<double> x, v, w, F, T;
+  Q4<double> q;
+};
+
+// What the local terms of a particle read besides its cotangent and moment: loaded
+// in one go, so that it is all in flight together (and, in the fused step, before
+// the barrier).
+struct LocalIn {
+  int b;
+  double minv, Iinv, mass, inertia;
+  V3<double> w0, T0, x1, Bd;
+  double f[12];  // field row
+};
+__device__ __forceinline__ LocalIn adj_local_in(const Dev& d, long i, const double* S0,
+                                                const double* S1, long long lvl) {
   const long N = d.n;
-  const bool free_p = d.bc[i] == 0;
-  const double h = 0.5 * d.dt;
-  V3<double> Fe{0, 0, 0}, Te{0, 0, 0}, vb{0, 0, 0}, wb{0, 0, 0};
-  if (free_p) {
-    const V3<double> cv = ldv(a.cv, N, i), cw = ldv(a.cw, N, i);
-    Fe = ldv(a.cF, N, i);
-    Te = ldv(a.cT, N, i);
-    vb = cv;
-    wb = cw;
-    if (mode == ADJ_STEP) {
-      Fe = Fe + (h * d.minv[i]) * cv;
-      Te = Te + (h * d.Iinv[i]) * cw;
-      // half-step angular velocity of the step, for the Richardson VJP
-      const V3<double> w0 = ldv(S0 + 10 * N, N, i), T0 = ldv(S0 + 16 * N, N, i);
-      st3(a.wh, N, i, w0 + (h * d.Iinv[i]) * T0);
-    }
-  }
-  // damping: F = -c m v', T = -c I w'
-  vb = vb - (d.damping * d.mass[i]) * Fe;
-  wb = wb - (d.damping * d.inertia[i]) * Te;
-  const V3<double> x1 = ldv(S1, N, i);
-  const V3<double> m = ldv(d.mu, N, i);
-  const V3<double> Bd = ldv(S1 + 19 * N, N, i);
+  LocalIn in{d.bc[i],          d.minv[i],     d.Iinv[i], d.mass[i], d.inertia[i],
+             ldv(S0 + 10 * N, N, i), ldv(S0 + 16 * N, N, i), ldv(S1, N, i), ldv(S1 + 19 * N, N, i), {}};
   const long long L = d.field_len;
   const long long row = ((lvl % L) + L) % L;
   const double* f = d.field + (row * d.M + d.mem[i]) * 12;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) in.f[k] = f[k];
+  return in;
+}
+
+// Post-kick VJP and the per-particle force terms (Zeeman, dipole torque,
+// damping). S1 is the state of the level whose forces are reversed; S0 the
+// state one level earlier (ADJ_STEP only).
+__device__ __forceinline__ void adj_local_of(const Dev& d, const Adj& a, long i, const LocalIn& in,
+                                             V3<double> m, const Cot& c, int mode) {
+  const long N = d.n;
+  const bool free_p = in.b == 0;
+  const double h = 0.5 * d.dt;
+  V3<double> Fe{0, 0, 0}, Te{0, 0, 0}, vb{0, 0, 0}, wb{0, 0, 0};
+  if (free_p) {
+    Fe = c.F;
+    Te = c.T;
+    vb = c.v;
+    wb = c.w;
+    if (mode == ADJ_STEP) {
+      Fe = Fe + (h * in.minv) * c.v;
+      Te = Te + (h * in.Iinv) * c.w;
+      // half-step angular velocity of the step, for the Richardson VJP
+      st3(a.wh, N, i, in.w0 + (h * in.Iinv) * in.T0);
+    }
+  }
+  // damping: F = -c m v', T = -c I w'
+  vb = vb - (d.damping * in.mass) * Fe;
+  wb = wb - (d.damping * in.inertia) * Te;
+  const V3<double> x1 = in.x1;
+  const double* f = in.f;
   const V3<double> Be{f[0] + f[3] * x1.x + f[4] * x1.y + f[5] * x1.z,
                       f[1] + f[6] * x1.x + f[7] * x1.y + f[8] * x1.z,
                       f[2] + f[9] * x1.x + f[10] * x1.y + f[11] * x1.z};
   // torque m x (B_dip + B_ext): m-bar += B x T-bar, B-bar = T-bar x m
-  const V3<double> Bt = Bd + Be;
+  const V3<double> Bt = in.Bd + Be;
   const V3<double> hb = cross(Te, m);
   // Zeeman force G^T m: m-bar += G F-bar
   const V3<double> GF{f[3] * Fe.x + f[4] * Fe.y + f[5] * Fe.z,
@@ -136,19 +159,19 @@ __device__ __forceinline__ void adj_local(const Dev& d, const Adj& a, long i, co
   for (int r = 0; r < 3; ++r)
     for (int c = 0; c < 3; ++c) a.fieldc[(3 + 3 * r + c) * N + i] = hbv[r] * xv[c] + mv[r] * Fv[c];
 }
+__device__ __forceinline__ void adj_local(const Dev& d, const Adj& a, long i, const double* S0,
+                                          const double* S1, int koff, int mode) {
+  const long N = d.n;
+  const Cot c{V3<double>{0, 0, 0}, ldv(a.cv, N, i), ldv(a.cw, N, i), ldv(a.cF, N, i), ldv(a.cT, N, i), {}};
+  adj_local_of(d, a, i, adj_local_in(d, i, S0, S1, *a.lbase + koff), ldv(d.mu, N, i), c, mode);
+}
 
 // ---------------------------------------------------------------- bonds
-// One thread per (input direction, bond): column `dir` of the bond's Jacobian
-// by a dual-number evaluation, contracted with the bond cotangent.
-__device__ __forceinline__ void adj_bond(const Dev& d, const Adj& a, const double* S1, long t) {
+// Column `dir` of bond k's Jacobian by a dual-number evaluation: the derivatives of
+// F, tau_s and tau_b + tau_t with respect to one of its 11 inputs.
+struct BondColumn { V3<double> F, Ts, Tbt; };
+__device__ __forceinline__ BondColumn bond_column(const Dev& d, const double* S1, long k, int dir) {
   const long N = d.n;
-  if (t >= 11 * N) return;
-  const int dir = (int)(t / N);
-  const long k = t - (long)dir * N;
-  if (!(d.bflags[k] & 1)) return;
-  const V3<double> Fb = ldv(a.Fe, N, k) - ldv(a.Fe, N, k + 1);
-  const V3<double> Tsb = ldv(a.Te, N, k) + ldv(a.Te, N, k + 1);
-  const V3<double> Tbb = ldv(a.Te, N, k) - ldv(a.Te, N, k + 1);
   const V3<double> x1 = ldv(S1, N, k), x2 = ldv(S1, N, k + 1);
   const Q4<double> q1 = ld4(S1 + 6 * N, N, k), q2 = ld4(S1 + 6 * N, N, k + 1);
   const V3<double> rref{d.bref[k], d.bref[N + k], d.bref[2 * N + k]};
@@ -161,9 +184,28 @@ __device__ __forceinline__ void adj_bond(const Dev& d, const Adj& a, const doubl
   Q4<DD> Q2{DD(q2.w, sd(7)), DD(q2.x, sd(8)), DD(q2.y, sd(9)), DD(q2.z, sd(10))};
   V3<DD> F, Ts, Tbt;
   bond_one<DD, DD>(X1, X2, Q1, Q2, rref, r0, K4, F, Ts, Tbt, nullptr);
-  a.bvjp[dir * N + k] = (F.x.d * Fb.x + F.y.d * Fb.y + F.z.d * Fb.z) +
-                        (Ts.x.d * Tsb.x + Ts.y.d * Tsb.y + Ts.z.d * Tsb.z) +
-                        (Tbt.x.d * Tbb.x + Tbt.y.d * Tbb.y + Tbt.z.d * Tbb.z);
+  return {V3<double>{F.x.d, F.y.d, F.z.d}, V3<double>{Ts.x.d, Ts.y.d, Ts.z.d},
+          V3<double>{Tbt.x.d, Tbt.y.d, Tbt.z.d}};
+}
+// The column contracted with the bond's cotangent.
+__device__ __forceinline__ double bond_contract(const Dev& d, const Adj& a, long k,
+                                                const BondColumn& c) {
+  const long N = d.n;
+  const V3<double> Fb = ldv(a.Fe, N, k) - ldv(a.Fe, N, k + 1);
+  const V3<double> Tsb = ldv(a.Te, N, k) + ldv(a.Te, N, k + 1);
+  const V3<double> Tbb = ldv(a.Te, N, k) - ldv(a.Te, N, k + 1);
+  return (c.F.x * Fb.x + c.F.y * Fb.y + c.F.z * Fb.z) +
+         (c.Ts.x * Tsb.x + c.Ts.y * Tsb.y + c.Ts.z * Tsb.z) +
+         (c.Tbt.x * Tbb.x + c.Tbt.y * Tbb.y + c.Tbt.z * Tbb.z);
+}
+// One thread per (input direction, bond).
+__device__ __forceinline__ void adj_bond(const Dev& d, const Adj& a, const double* S1, long t) {
+  const long N = d.n;
+  if (t >= 11 * N) return;
+  const int dir = (int)(t / N);
+  const long k = t - (long)dir * N;
+  if (!(d.bflags[k] & 1)) return;
+  a.bvjp[dir * N + k] = bond_contract(d, a, k, bond_column(d, S1, k, dir));
 }
 
 // ---------------------------------------------------------------- dipoles
@@ -409,75 +451,103 @@ __global__ __launch_bounds__(256) void k_adj_forces(Dev d, Adj a, const double* 
 }
 
 // ---------------------------------------------------------------- gather
+// What the gather of a particle reads besides its force terms.
+struct GatherIn {
+  uint8_t bf;
+  int b;
+  double minv, Iinv;
+  V3<double> cx, xloc, mloc, mb, mbbar, vbar, wbar, wh;
+  Q4<double> cq, q1, q0;
+};
+__device__ __forceinline__ GatherIn adj_gather_in(const Dev& d, const Adj& a, long i,
+                                                  const double* S0, const double* S1) {
+  const long N = d.n;
+  return {d.bflags[i],       d.bc[i],            d.minv[i],          d.Iinv[i],
+          ldv(a.cx, N, i),   ldv(a.xloc, N, i),  ldv(a.mloc, N, i),  ldv(d.mb, N, i),
+          ldv(a.mbbar, N, i), ldv(a.vbar, N, i), ldv(a.wbar, N, i),  ldv(a.wh, N, i),
+          ld4(a.cq, N, i),   ld4(S1 + 6 * N, N, i), ld4(S0 + 6 * N, N, i)};
+}
+
 // Assemble x-bar and q-bar of the level, push m-bar through m = q m_body q*,
-// then reverse the pre kick (ADJ_STEP) or write the initial-state gradients
-// (ADJ_PREPARE).
+// then reverse the pre kick (ADJ_STEP: returns the cotangent of S0) or write the
+// initial-state gradients (ADJ_PREPARE). bond(dir, which) is column `dir` of the
+// particle's bond as its first (0) or second (1) particle; dipoles(xb, mbar) adds
+// the dipole terms and contact() is the contact term.
+template <class B, class D, class C>
+__device__ __forceinline__ Cot adj_gather_of(const Dev& d, const Adj& a, long i, const GatherIn& in,
+                                             int mode, const rod_gradients& gx, B&& bond,
+                                             D&& dipoles, C&& contact) {
+  const long N = d.n;
+  V3<double> xb = in.cx + in.xloc;
+  Q4<double> qb = in.cq;
+  if (in.bf & 1) {  // bond (i, i+1): i is particle 1
+    xb = xb - V3<double>{bond(0, 0), bond(1, 0), bond(2, 0)};
+    qb = qadd(qb, Q4<double>{bond(3, 0), bond(4, 0), bond(5, 0), bond(6, 0)});
+  }
+  if (in.bf & 2) {  // bond (i-1, i): i is particle 2
+    xb = xb + V3<double>{bond(0, 1), bond(1, 1), bond(2, 1)};
+    qb = qadd(qb, Q4<double>{bond(7, 1), bond(8, 1), bond(9, 1), bond(10, 1)});
+  }
+  V3<double> mbar = in.mloc;
+  if (d.dipole_on) dipoles(xb, mbar);
+  if (d.contact_on) xb = xb + contact();
+  // m = q m_body q*: m_body-bar += q* m-bar q; q-bar += -2 (0, m-bar) q (0, m_body)
+  const Q4<double> q1 = in.q1;
+  st3(a.mbbar, N, i, in.mbbar + qrot_inv(q1, mbar));
+  qb = qadd(qb, qscale(-2.0, qmul(qmul(qv(mbar), q1), qv(in.mb))));
+  const V3<double> z{0, 0, 0};
+  Cot c{xb, z, z, z, z, {0, 0, 0, 0}};
+  if (mode == ADJ_STEP) {
+    if (in.b == 0) {
+      c.w = in.wbar;
+      richardson_vjp(in.q0, in.wh, d.dt, qb, c.q, c.w);
+      c.v = in.vbar + d.dt * xb;
+      const double h = 0.5 * d.dt;
+      c.F = (h * in.minv) * c.v;
+      c.T = (h * in.Iinv) * c.w;
+    } else if (in.b == 1) {
+      c.q = qb;
+    }
+  } else {
+    if (gx.x0) st3(gx.x0, N, i, xb);
+    if (gx.v0) st3(gx.v0, N, i, in.b == 0 ? in.vbar : z);
+    if (gx.w0) st3(gx.w0, N, i, in.b == 0 ? in.wbar : z);
+    if (gx.q0) {
+      // q was normalised from the raw input: project out the radial part.
+      Q4<double> g{0, 0, 0, 0};
+      if (in.b != 2) g = qadd(qb, qscale(-qdot(q1, qb), q1));
+      st4(gx.q0, N, i, g);
+    }
+  }
+  return c;
+}
+__device__ __forceinline__ void store_cot(const Adj& a, long N, long i, const Cot& c) {
+  st3(a.cx, N, i, c.x);
+  st3(a.cv, N, i, c.v);
+  st4(a.cq, N, i, c.q);
+  st3(a.cw, N, i, c.w);
+  st3(a.cF, N, i, c.F);
+  st3(a.cT, N, i, c.T);
+}
+
+// The gather with the terms of the separate force launch.
 __device__ __forceinline__ void adj_gather(const Dev& d, const Adj& a, long i, const double* S0,
                                            const double* S1, int nslot_max, int mode,
                                            const rod_gradients& gx) {
   const long N = d.n;
-  const uint8_t bf = d.bflags[i];
-  V3<double> xb = ldv(a.cx, N, i) + ldv(a.xloc, N, i);
-  Q4<double> qb = ld4(a.cq, N, i);
-  if (bf & 1) {  // bond (i, i+1): i is particle 1
-    xb = xb - V3<double>{a.bvjp[i], a.bvjp[N + i], a.bvjp[2 * N + i]};
-    qb = qadd(qb, Q4<double>{a.bvjp[3 * N + i], a.bvjp[4 * N + i], a.bvjp[5 * N + i], a.bvjp[6 * N + i]});
-  }
-  if (bf & 2) {  // bond (i-1, i): i is particle 2
-    const long k = i - 1;
-    xb = xb + V3<double>{a.bvjp[k], a.bvjp[N + k], a.bvjp[2 * N + k]};
-    qb = qadd(qb, Q4<double>{a.bvjp[7 * N + k], a.bvjp[8 * N + k], a.bvjp[9 * N + k], a.bvjp[10 * N + k]});
-  }
-  V3<double> mbar = ldv(a.mloc, N, i);
-  if (d.dipole_on) {
-    const int S = d.mslots[d.mem[i]];
-    for (int s = 0; s < S && s < nslot_max; ++s) {
-      const double* p = d.dpart + (long)s * 6 * N;
-      xb = xb + V3<double>{p[i], p[N + i], p[2 * N + i]};
-      mbar = mbar + V3<double>{p[3 * N + i], p[4 * N + i], p[5 * N + i]};
-    }
-  }
-  if (d.contact_on) xb = xb + ldv(d.cF, N, i);
-  // m = q m_body q*: m_body-bar += q* m-bar q; q-bar += -2 (0, m-bar) q (0, m_body)
-  const Q4<double> q1 = ld4(S1 + 6 * N, N, i);
-  const V3<double> mbody = ldv(d.mb, N, i);
-  st3(a.mbbar, N, i, ldv(a.mbbar, N, i) + qrot_inv(q1, mbar));
-  qb = qadd(qb, qscale(-2.0, qmul(qmul(qv(mbar), q1), qv(mbody))));
-  const int b = d.bc[i];
-  const V3<double> z{0, 0, 0};
-  if (mode == ADJ_STEP) {
-    V3<double> vb = ldv(a.vbar, N, i), wb = ldv(a.wbar, N, i);
-    Q4<double> qn{0, 0, 0, 0};
-    if (b == 0) {
-      const Q4<double> q0 = ld4(S0 + 6 * N, N, i);
-      richardson_vjp(q0, ldv(a.wh, N, i), d.dt, qb, qn, wb);
-      vb = vb + d.dt * xb;
-      const double h = 0.5 * d.dt;
-      st3(a.cx, N, i, xb);
-      st3(a.cv, N, i, vb);
-      st4(a.cq, N, i, qn);
-      st3(a.cw, N, i, wb);
-      st3(a.cF, N, i, (h * d.minv[i]) * vb);
-      st3(a.cT, N, i, (h * d.Iinv[i]) * wb);
-    } else {
-      st3(a.cx, N, i, xb);
-      st4(a.cq, N, i, b == 1 ? qb : qn);
-      st3(a.cv, N, i, z);
-      st3(a.cw, N, i, z);
-      st3(a.cF, N, i, z);
-      st3(a.cT, N, i, z);
-    }
-  } else {
-    if (gx.x0) st3(gx.x0, N, i, xb);
-    if (gx.v0) st3(gx.v0, N, i, b == 0 ? ldv(a.vbar, N, i) : z);
-    if (gx.w0) st3(gx.w0, N, i, b == 0 ? ldv(a.wbar, N, i) : z);
-    if (gx.q0) {
-      // q was normalised from the raw input: project out the radial part.
-      Q4<double> g{0, 0, 0, 0};
-      if (b != 2) g = qadd(qb, qscale(-qdot(q1, qb), q1));
-      st4(gx.q0, N, i, g);
-    }
-  }
+  const Cot c = adj_gather_of(
+      d, a, i, adj_gather_in(d, a, i, S0, S1), mode, gx,
+      [&](int dir, int which) { return a.bvjp[dir * N + i - which]; },
+      [&](V3<double>& xb, V3<double>& mbar) {
+        const int S = d.mslots[d.mem[i]];
+        for (int s = 0; s < S && s < nslot_max; ++s) {
+          const double* p = d.dpart + (long)s * 6 * N;
+          xb = xb + V3<double>{p[i], p[N + i], p[2 * N + i]};
+          mbar = mbar + V3<double>{p[3 * N + i], p[4 * N + i], p[5 * N + i]};
+        }
+      },
+      [&] { return ldv(d.cF, N, i); });
+  if (mode == ADJ_STEP) store_cot(a, N, i, c);
 }
 
 // Cell list of level lvl is done with: empty it.
@@ -522,6 +592,232 @@ __global__ __launch_bounds__(256) void k_adj_gather(Dev v, Adj a, const double* 
   if (i < v.n) adj_gather(v, a, i, S0, S1, nslot_max, mode, gx);
 }
 
+// ---------------------------------------------------------------- small systems
+// Reverse of a whole step in one launch for systems whose forward steps are single
+// launches (k_step.hip): a workgroup owns ADJ_T particles, a wave sums each one's
+// dipole and contact terms, one wave evaluates the 11 Jacobian columns of the
+// ADJ_T + 1 bonds around them, and one thread per particle then does the gather of
+// the level and the local terms of the level before. Those publish what other
+// particles need of them (AdjPub) in the set that nobody reads in this launch.
+// Against a local and a force launch per level (8.8 and 6.6 us at N = 256, plus the
+// gap between them): 18 -> 8.2 us per level (11.5 when the particle threads loaded
+// their inputs after the barrier instead of before it).
+constexpr int ADJ_T = 4;
+
+// Dipole and contact terms of target i of the member [b, e), by one wave, into
+// out[0..6) (x-bar, m-bar before the factor C) and out[6..9) (contact x-bar).
+// Contact candidates are marked as in small_target; [xlo, xhi] are excluded.
+__device__ __forceinline__ void adj_small_target(const Dev& d, const Adj& a, const double* S1, int i,
+                                                 int b, int e, int xlo, int xhi, double* out) {
+  constexpr int U = 2;  // rounds in flight
+  const long N = d.n;
+  const int lane = threadIdx.x & 63;
+  const V3<double> xi = ldv(S1, N, i), mi = ldv(d.mu, N, i), gi = ldv(a.Fe, N, i),
+                   hi = ldv(a.h, N, i);
+  const bool dip = d.dipole_on, con = d.contact_on;
+  const double rc2 = d.rc * d.rc;
+  const unsigned span = (unsigned)(xhi - xlo);
+  V3<double> xb{0, 0, 0}, mb{0, 0, 0};
+  Fix3 f{};
+  bool hit = false;
+  unsigned near = 0;
+  int round = 0, base = b;
+  for (int j0 = b; j0 < e; j0 += U * 64) {
+    V3<double> xj[U], mj[U], gj[U], hj[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {  // loads first; out-of-range entries read the first source
+      const int j = j0 + 64 * u + lane < e ? j0 + 64 * u + lane : b;
+      xj[u] = ldv(S1, N, j); mj[u] = ldv(d.mu, N, j); gj[u] = ldv(a.Fe, N, j); hj[u] = ldv(a.h, N, j);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 64 * u + lane;
+      if (j0 + 64 * u >= e) break;  // the whole wave
+      if (con && j < e && r2x(xi, xj[u]) < rc2 && (unsigned)(j - xlo) > span) near |= 1u << (round + u);
+      if (!dip || j >= e || j == i) continue;
+      V3<double> dr, da, db;
+      phi_grad(xi - xj[u], mi, mj[u], gi, hi, dr, da, db);  // i as target
+      xb = xb - dr;
+      mb = mb - da;
+      phi_grad(xj[u] - xi, mj[u], mi, gj[u], hj[u], dr, da, db);  // i as source
+      xb = xb + dr;
+      mb = mb - db;
+    }
+    round += U;
+    if (con && (round == 32 || j0 + U * 64 >= e)) {
+      while (__any(near != 0u)) {
+        if (near != 0u) {
+          const int j = base + lane + 64 * (__ffs((int)near) - 1);
+          near &= near - 1u;
+          hit = true;
+          const V3<double> xc = ldv(S1, N, j);
+          const double r2 = r2x(xi, xc);
+          const double r = ::sqrt(r2);
+          const V3<double> dd = xi - xc, gv = gi - ldv(a.Fe, N, j);
+          const double s1 = d.kc * (d.rc / r - 1.0);
+          const double s2 = d.kc * d.rc * dot(dd, gv) / (r * r2);
+          fix_add(f, s1 * gv - s2 * dd, d.fix_scale[0], d.flags + FLAG_CONTACT_RANGE);
+        }
+      }
+      round = 0;
+      base = j0 + U * 64;
+    }
+  }
+  if (con) {
+    V3<double> c{0.0, 0.0, 0.0};
+    if (__any(hit)) c = wave_value<64>(f, d.fix_inv[0]);
+    if (lane == 0) { out[6] = c.x; out[7] = c.y; out[8] = c.z; }
+  }
+  if (dip) {
+    double v6[6] = {xb.x, xb.y, xb.z, mb.x, mb.y, mb.z};
+    wave_sum6(v6, out);
+  }
+}
+
+// `d` and `a` with what a level publishes in `p` and fieldc.
+__device__ __forceinline__ void adj_publish(Dev& d, Adj& a, const AdjPub& p, double* fieldc) {
+  d.mu = p.mu;
+  a.Fe = p.Fe; a.Te = p.Te; a.h = p.h;
+  a.fieldc = fieldc;
+}
+
+// The last level of a segment (state S1, the step from S0): its local terms.
+__global__ __launch_bounds__(64) void k_adj_open(Dev d, Adj a, AdjPub p, const double* S0,
+                                                 const double* S1, int koff, double* fieldc) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= d.n) return;
+  adj_publish(d, a, p, fieldc);
+  st3(d.mu, d.n, i, qrot(ld4(S1 + 6 * d.n, d.n, i), ldv(d.mb, d.n, i)));
+  adj_local(d, a, i, S0, S1, koff, ADJ_STEP);
+}
+
+// Bond Jacobians of `levels` consecutive levels from the state S of the first (their
+// states stride apart), one thread per level, column and bond, into
+// J[level][column][9][N]. They depend on the recorded states alone, so they are
+// taken for many levels at once, at full occupancy, and leave the level-to-level
+// chain (N = 256: 23 us for 100 levels; 1.4 us per level inside the step).
+__global__ __launch_bounds__(256) void k_adj_jacobians(Dev d, const double* S, long stride, int levels,
+                                                       double* J) {
+  const long N = d.n;
+  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long col = t / N, k = t - col * N;  // level * 11 + column
+  if (col >= 11L * levels || !(d.bflags[k] & 1)) return;
+  const int dir = (int)(col % 11);
+  const BondColumn c = bond_column(d, S + (col / 11) * stride, k, dir);
+  double* o = J + col * 9 * N;
+  st3(o, N, k, c.F);
+  st3(o + 3 * N, N, k, c.Ts);
+  st3(o + 6 * N, N, k, c.Tbt);
+}
+
+// Level lbase + koff with state S1 (the step from S0): force terms and gather, then
+// (SP set: the state before S0) the local terms of S0's level, published in `next`.
+__global__ __launch_bounds__(64 * (ADJ_T + 2)) void k_adj_step(Dev d, Adj a, AdjPub now, AdjPub next,
+                                                               const double* SP, const double* S0,
+                                                               const double* S1, const double* J,
+                                                               int koff, double* fieldc) {
+  __shared__ double sums[ADJ_T][10];
+  __shared__ double cols[11][ADJ_T + 1];
+  const long N = d.n;
+  const int i0 = blockIdx.x * ADJ_T;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (wave < ADJ_T) {
+    adj_publish(d, a, now, nullptr);
+    const int i = i0 + wave;
+    if (i < N) {
+      int b = 0, e = (int)N, xlo, xhi;
+      if (d.M > 1) {
+        const int m = d.mem[i];
+        b = d.mrange[2 * m];
+        e = d.mrange[2 * m + 1];
+      }
+      excluded_range(d, i, xlo, xhi);
+      adj_small_target(d, a, S1, i, b, e, xlo, xhi, sums[wave]);
+    }
+    __syncthreads();
+    return;
+  }
+  if (wave == ADJ_T) {  // bonds i0 - 1 .. i0 + ADJ_T - 1, a lane per column
+    adj_publish(d, a, now, nullptr);
+    const int dir = lane / (ADJ_T + 1), u = lane - dir * (ADJ_T + 1);
+    const long k = i0 - 1 + u;
+    if (dir < 11 && k >= 0 && k < N && (d.bflags[k] & 1)) {
+      const double* o = J + dir * 9 * N;
+      cols[dir][u] = bond_contract(d, a, k, BondColumn{ld3(o, N, k), ld3(o + 3 * N, N, k), ld3(o + 6 * N, N, k)});
+    }
+    __syncthreads();
+    return;
+  }
+  const bool valid = lane < ADJ_T && i0 + lane < N;
+  const long i = valid ? i0 + lane : i0;
+  adj_publish(d, a, next, fieldc);
+  const GatherIn in = adj_gather_in(d, a, i, S0, S1);
+  LocalIn loc{};
+  if (SP) loc = adj_local_in(d, i, SP, S0, *a.lbase + koff - 1);
+  __syncthreads();
+  if (!valid) return;
+  const double* u = sums[lane];
+  const Cot c = adj_gather_of(
+      d, a, i, in, ADJ_STEP, rod_gradients{},
+      [&](int dir, int which) { return cols[dir][lane + 1 - which]; },
+      [&](V3<double>& xb, V3<double>& mbar) {
+        xb = xb + d.C * V3<double>{u[0], u[1], u[2]};
+        mbar = mbar + d.C * V3<double>{u[3], u[4], u[5]};
+      },
+      [&] { return V3<double>{u[6], u[7], u[8]}; });
+  store_cot(a, N, i, c);
+  if (SP) {
+    const V3<double> m = qrot(in.q0, in.mb);
+    st3(d.mu, N, i, m);
+    adj_local_of(d, a, i, loc, m, c, ADJ_STEP);
+  }
+}
+static_assert(11 * (ADJ_T + 1) <= 64, "a lane per bond column");
+
+// Field gradient of a segment: the member sums of every level (a workgroup each),
+// then their addition to the table's rows, latest level first.
+__global__ __launch_bounds__(256) void k_adj_field_sums(Dev d, const double* fieldc, double* part) {
+  __shared__ double red[12][256];
+  const int mem = blockIdx.x, koff = 1 + blockIdx.y;
+  const int b = d.mrange[2 * mem], e = d.mrange[2 * mem + 1];
+  const long N = d.n;
+  const double* f = fieldc + (long)koff * 12 * N;
+  double s[12];
+  for (int k = 0; k < 12; ++k) s[k] = 0.0;
+  for (int i = b + threadIdx.x; i < e; i += blockDim.x)
+    for (int k = 0; k < 12; ++k) s[k] += f[k * N + i];
+  for (int k = 0; k < 12; ++k) red[k][threadIdx.x] = s[k];
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w)
+      for (int k = 0; k < 12; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x < 12) part[((long)koff * d.M + mem) * 12 + threadIdx.x] = red[threadIdx.x][0];
+}
+__global__ __launch_bounds__(64) void k_adj_field_rows(Dev d, Adj a, const double* __restrict__ part,
+                                                       double* __restrict__ bar, int len) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= 12 * d.M) return;
+  const long long L = d.field_len;
+  const long long base = *a.lbase;
+  long long at = -1;  // the row being added to
+  double sum = 0.0;
+#pragma unroll 8
+  for (int koff = len; koff > 0; --koff) {
+    const double p = part[(long)koff * d.M * 12 + t];
+    const long long lvl = base + koff, row = ((lvl % L) + L) % L;
+    if (row != at) {
+      if (at >= 0) bar[at * d.M * 12 + t] = sum;
+      at = row;
+      sum = bar[at * d.M * 12 + t];
+    }
+    sum += p;
+  }
+  if (at >= 0) bar[at * d.M * 12 + t] = sum;
+}
+
 __global__ void k_set_level(long long* p, long long v) {
   if (threadIdx.x == 0 && blockIdx.x == 0) { p[0] = v; p[1] = v; }
 }
@@ -558,6 +854,7 @@ static int adalloc(std::vector<void*>& allocs, T** p, size_t count) {
 int tape_init(Tape& t, const Dev& d, int every, int capacity, std::vector<void*>& allocs) {
   t.every = every;
   t.capacity = capacity;
+  t.allocs = &allocs;
   if (capacity <= 0) return ROD_OK;
   const size_t N = d.n;
   const size_t nck = (size_t)capacity / every + 1;
@@ -665,10 +962,28 @@ static int reverse_gather(Tape& t, const Dev& d, int max_slots, hipStream_t s, c
 // kick closes slot k (full-step v and w, forces, dipole field) and writes the
 // advanced state into slot k + 1.
 static int recompute(Tape& t, const Dev& d, int precision, const DipWork* work, int nwork,
-                     hipStream_t s, int len) {
+                     const TapeSmall& small, hipStream_t s, int len) {
   const long N = d.n;
   const size_t SP = SEG_PLANES * (size_t)N;
   Dev v = view(d, t.seg + SP, t.a.level);
+  if (small.mu) {  // the fused steps: level k reads its slot and writes the next
+    v.src = t.seg;
+    v.lazy_cells = 1;
+    v.far_ok = 0;
+    ACHK(launch_pre(v, PRE_STEP, s));
+    for (int k = 1; k <= len; ++k) {
+      double* Sk = t.seg + k * SP;
+      Dev w = view(d, Sk, t.a.level);
+      w.lc = k & 1 ? 1 : 2;
+      double* mu[2] = {d.mu, small.mu};
+      float* muf[2] = {d.muf, small.muf};
+      w.mu = mu[(k + 1) & 1]; w.muf = muf[(k + 1) & 1];
+      const StepOut o{Sk + SP, Sk + SP + 3 * N, Sk + SP + 6 * N, Sk + SP + 10 * N,
+                      mu[k & 1], muf[k & 1], Sk + 19 * N, k == len, 1};
+      ACHK(launch_step(w, precision, o, s));
+    }
+    return ROD_OK;
+  }
   v.src = t.seg;  // the pre kernel reads step 0 and writes step 1
   ACHK(launch_pre(v, PRE_STEP, s));
   v.src = nullptr;
@@ -697,6 +1012,42 @@ static int reverse_segment(Tape& t, const Dev& d, const DipWork* work, int nwork
   return reverse_gather(t, d, max_slots, s, t.seg, t.seg + SP, 1, ADJ_STEP, rod_gradients{});
 }
 
+// The same by the fused reverse steps of small systems.
+static int reverse_small(Tape& t, const Dev& d, hipStream_t s, int len) {
+  const long N = d.n;
+  const size_t SP = SEG_PLANES * (size_t)N;
+  const Adj& a = t.a;
+  const AdjPub sets[2] = {{a.Fe, a.Te, a.h, d.mu},
+                          {t.pub, t.pub + 3 * N, t.pub + 6 * N, t.pub + 9 * N}};
+  const int chunk = t.jac_levels;
+  double* S = t.seg + len * SP;
+  hipLaunchKernelGGL(k_adj_open, dim3(nblk(N, 64)), dim3(64), 0, s, d, a, sets[len & 1],
+                     (const double*)(S - SP), (const double*)S, len, t.fieldc + (size_t)len * 12 * N);
+  ACHK(hipGetLastError());
+  for (int k = len, first = len + 1; k >= 1; --k, S -= SP) {
+    if (k < first) {  // Jacobians of the levels [first, k]
+      first = std::max(1, k - chunk + 1);
+      const int m = k - first + 1;
+      hipLaunchKernelGGL(k_adj_jacobians, dim3(nblk(11L * m * N, 256)), dim3(256), 0, s, d,
+                         (const double*)(t.seg + first * SP), (long)SP, m, t.jac);
+      ACHK(hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_adj_step, dim3(nblk(N, ADJ_T)), dim3(64 * (ADJ_T + 2)), 0, s, d, a,
+                       sets[k & 1], sets[1 - (k & 1)], k > 1 ? (const double*)(S - 2 * SP) : nullptr,
+                       (const double*)(S - SP), (const double*)S,
+                       (const double*)(t.jac + (size_t)(k - first) * 99 * N), k,
+                       t.fieldc + (size_t)(k - 1) * 12 * N);
+    ACHK(hipGetLastError());
+  }
+  hipLaunchKernelGGL(k_adj_field_sums, dim3(d.M, len), dim3(256), 0, s, d, (const double*)t.fieldc,
+                     t.fieldp);
+  ACHK(hipGetLastError());
+  hipLaunchKernelGGL(k_adj_field_rows, dim3(nblk(12 * d.M, 64)), dim3(64), 0, s, d, a,
+                     (const double*)t.fieldp, a.fieldbar, len);
+  ACHK(hipGetLastError());
+  return ROD_OK;
+}
+
 template <class F>
 static int capture(hipStream_t s, hipGraphExec_t* out, F body) {
   hipGraph_t g = nullptr;
@@ -718,7 +1069,8 @@ void tape_release(Tape& t) {
 }
 
 int adjoint_run(Tape& t, const Dev& d, int precision, const DipWork* work, int nwork,
-                hipStream_t s, int64_t end_step, const rod_cotangent* gy, rod_gradients* gx) {
+                int max_slots, const TapeSmall& small, hipStream_t s, int64_t end_step,
+                const rod_cotangent* gy, rod_gradients* gx) {
   const long N = d.n;
   const int64_t T = end_step - t.start_step;
   if (T <= 0) return rodmx_fail(ROD_E_NOTAPE, "no recorded steps");
@@ -731,12 +1083,26 @@ int adjoint_run(Tape& t, const Dev& d, int precision, const DipWork* work, int n
   if (gy->w) ACHK(hipMemcpyAsync(a.cw, gy->w, b3, hipMemcpyDeviceToDevice, s));
   ACHK(hipMemsetAsync(a.mbbar, 0, b3, s));
   ACHK(hipMemsetAsync(a.fieldbar, 0, (size_t)d.field_len * d.M * 12 * sizeof(double), s));
-  int max_slots = 1;
-  {
-    std::vector<int> ms(d.M);
-    ACHK(hipMemcpy(ms.data(), d.mslots, d.M * sizeof(int), hipMemcpyDeviceToHost));
-    for (int m : ms) max_slots = std::max(max_slots, m);
+  if (small.mu && !t.pub) {
+    double* pub = nullptr;
+    ATRY(adalloc(*t.allocs, &t.fieldc, (size_t)(t.every + 1) * 12 * N));
+    ATRY(adalloc(*t.allocs, &t.fieldp, (size_t)(t.every + 1) * 12 * d.M));
+    // Jacobians of as many levels as fit in 128 MiB (at least one)
+    t.jac_levels = (int)std::max<size_t>(1, std::min<size_t>(t.every, (128u << 20) / (99 * sizeof(double) * N)));
+    ATRY(adalloc(*t.allocs, &t.jac, (size_t)t.jac_levels * 99 * N));
+    ATRY(adalloc(*t.allocs, &pub, 12 * (size_t)N));
+    t.pub = pub;
   }
+  auto redo = [&](int len, int64_t s0) -> int {
+    if (!small.many) return recompute(t, d, precision, work, nwork, small, s, len);
+    Dev v = view(d, t.seg, a.level);
+    ACHK(launch_steps(v, precision, small.many, s0, len, s, t.seg, SEG_PLANES * N));
+    return ROD_OK;
+  };
+  auto undo = [&](int len) {
+    return small.mu ? reverse_small(t, d, s, len)
+                    : reverse_segment(t, d, work, nwork, max_slots, s, len);
+  };
   const int64_t nseg = (T + t.every - 1) / t.every;
   for (int64_t sg = nseg - 1; sg >= 0; --sg) {
     const int64_t s0 = t.start_step + sg * t.every;
@@ -750,15 +1116,16 @@ int adjoint_run(Tape& t, const Dev& d, int precision, const DipWork* work, int n
                        a.levels, t.every + 1, (long long)s0);
     ACHK(hipGetLastError());
     if (len == t.every) {
-      if (!t.g_recompute)
-        ATRY(capture(s, &t.g_recompute, [&] { return recompute(t, d, precision, work, nwork, s, len); }));
-      if (!t.g_reverse)
-        ATRY(capture(s, &t.g_reverse, [&] { return reverse_segment(t, d, work, nwork, max_slots, s, len); }));
-      ACHK(hipGraphLaunch(t.g_recompute, s));
+      // (a many-steps launch takes its level as an argument and is not captured)
+      if (!t.g_recompute && !small.many)
+        ATRY(capture(s, &t.g_recompute, [&] { return redo(len, s0); }));
+      if (!t.g_reverse) ATRY(capture(s, &t.g_reverse, [&] { return undo(len); }));
+      if (small.many) ATRY(redo(len, s0));
+      else ACHK(hipGraphLaunch(t.g_recompute, s));
       ACHK(hipGraphLaunch(t.g_reverse, s));
     } else {
-      ATRY(recompute(t, d, precision, work, nwork, s, len));
-      ATRY(reverse_segment(t, d, work, nwork, max_slots, s, len));
+      ATRY(redo(len, s0));
+      ATRY(undo(len));
     }
   }
   // the initial force evaluation: dipole field of the start state, then its reverse

@@ -95,13 +95,6 @@ template <class R> __device__ __forceinline__ const R* moments(const Dev& d);
 template <> __device__ __forceinline__ const float* moments(const Dev& d) { return d.muf; }
 template <> __device__ __forceinline__ const double* moments(const Dev& d) { return d.mu; }
 
-// Index range of the particles of i's rod within the exclusion depth of i.
-__device__ __forceinline__ void excluded_range(const Dev& d, int i, int& lo, int& hi) {
-  const int rod = d.rod[i], b = d.rod_off[rod], e = d.rod_off[rod + 1];
-  lo = i - b > d.depth ? i - d.depth : b;
-  hi = e - 1 - i > d.depth ? i + d.depth : e - 1;
-}
-
 // One step's forces, closing half-kick and (unless o.last) the next step's
 // opening half-kick, drift and rotation, for T particles per workgroup: NW waves
 // take the targets in turn, the last wave the T + 1 bonds around them and then
@@ -172,6 +165,7 @@ __global__ __launch_bounds__(64 * (NW + 1)) void k_step(Dev d, StepOut o) {
   gather_sum<HM>(d, i, ROD_TERM_ALL, fr, p, bd, mass, inertia, Fd, Bd, cF, cT, F, T_);
   kick(d, i, F, T_, p, o.keep, o.keep || o.last);
   if (o.last) {  // the state of the level, into the caller's planes
+    if (o.keep) return;  // (a recorded level's own hold it)
     st3(o.x, N, i, p.x);
     st3(o.v, N, i, p.v);
     st4(o.q, N, i, p.q);
@@ -206,8 +200,12 @@ struct StepsSmem {
   int xr[STEPS_MAX][2];                    // index range of excluded neighbours
 };
 
+// With rec (a recorded run) level lvl0 + s goes to rec + s * rec_stride, in the
+// planes of a recorded state followed by the dipole field, and the state read is
+// left as it was.
 template <class R, bool DAMP, int W>
-__global__ __launch_bounds__(STEPS_THREADS) void k_steps(Dev d, long long lvl0, int n) {
+__global__ __launch_bounds__(STEPS_THREADS) void k_steps(Dev d, long long lvl0, int n, double* rec,
+                                                         long rec_stride) {
   constexpr long PM = STEPS_MAX;
   __shared__ StepsSmem S;
   __shared__ R sm[3 * STEPS_MAX];  // moments
@@ -301,18 +299,29 @@ __global__ __launch_bounds__(STEPS_THREADS) void k_steps(Dev d, long long lvl0, 
       if (d.contact_on) cF = V3<double>{u[10], u[11], u[12]};
       gather_sum<false>(d, i, ROD_TERM_ALL, S.field, p, bd, S.pc[5 * PM + l], S.pc[6 * PM + l], Fd, Bd,
                      cF, V3<double>{0.0, 0.0, 0.0}, F, T);
-      kick(d, i, F, T, p, s == n, s == n);
+      const bool out = s == n && !rec;
+      kick(d, i, F, T, p, out, out);
+      if (rec) {
+        double* r = rec + s * rec_stride;
+        st3(r, N, i, p.x);
+        st3(r + 3 * N, N, i, p.v);
+        st4(r + 6 * N, N, i, p.q);
+        st3(r + 10 * N, N, i, p.w);
+        st3(r + 13 * N, N, i, F);
+        st3(r + 16 * N, N, i, T);
+        st3(r + 19 * N, N, i, Bd);
+      }
       if (s < n) {
         advance_particle(d, p.b, L + 1, p.x, p.v, p.q, p.w, F, T, p.minv, p.Iinv);
         publish(p);
-      } else {
+      } else if (out) {
         st3(d.x, N, i, p.x);
         st4(d.q, N, i, p.q);
       }
     }
     __syncthreads();
   }
-  if (b == 0 && tid == 0) d.step[0] = lvl0 + n;
+  if (b == 0 && tid == 0 && !rec) d.step[0] = lvl0 + n;
 }
 
 template <class R, bool HM, bool DAMP>
@@ -325,10 +334,11 @@ static void step_variant(const Dev& d, const StepOut& o, hipStream_t s) {
                        0, s, d, o);
 }
 template <class R, bool DAMP>
-static void steps_variant(const Dev& d, int max_member, long long lvl0, int n, hipStream_t s) {
+static void steps_variant(const Dev& d, int max_member, long long lvl0, int n, double* rec,
+                          long rec_stride, hipStream_t s) {
   const dim3 g((unsigned)d.M), b(STEPS_THREADS);
-  if (max_member <= 16) hipLaunchKernelGGL((k_steps<R, DAMP, 16>), g, b, 0, s, d, lvl0, n);
-  else hipLaunchKernelGGL((k_steps<R, DAMP, 32>), g, b, 0, s, d, lvl0, n);
+  if (max_member <= 16) hipLaunchKernelGGL((k_steps<R, DAMP, 16>), g, b, 0, s, d, lvl0, n, rec, rec_stride);
+  else hipLaunchKernelGGL((k_steps<R, DAMP, 32>), g, b, 0, s, d, lvl0, n, rec, rec_stride);
 }
 
 template <class F>
@@ -354,9 +364,9 @@ hipError_t launch_step(const Dev& d, int precision, const StepOut& o, hipStream_
 }
 
 hipError_t launch_steps(const Dev& d, int precision, int max_member, long long lvl0, int n,
-                        hipStream_t s) {
+                        hipStream_t s, double* rec, long rec_stride) {
   by_form(d, precision, [&](auto r, auto, auto damp) {
-    steps_variant<decltype(r), decltype(damp)::value>(d, max_member, lvl0, n, s);
+    steps_variant<decltype(r), decltype(damp)::value>(d, max_member, lvl0, n, rec, rec_stride, s);
   });
   return hipGetLastError();
 }

@@ -32,6 +32,22 @@ struct Adj {
   long long* levels;    // [every + 1][3]: counters of the reverse view of level lbase + k
 };
 
+// What the rest of the system sees of a level being reversed: the cotangents of
+// force and torque, of the dipole field, and the moments. The fused reverse steps
+// of small systems alternate between two sets, since other workgroups still read
+// the later level's.
+struct AdjPub {
+  double *Fe, *Te, *h, *mu;
+};
+
+// Second moment planes and the shape of the fused steps (k_step.hip), when the
+// forward takes them (mu null otherwise).
+struct TapeSmall {
+  double* mu = nullptr;
+  float* muf = nullptr;
+  int many = 0;  // members fit the many-steps kernel: their largest size
+};
+
 struct Tape {
   int every = 0, capacity = 0;
   bool active = false;
@@ -41,13 +57,23 @@ struct Tape {
   Adj a{};
   // graphs of one full segment: recompute and reverse (captured on first use)
   hipGraphExec_t g_recompute = nullptr, g_reverse = nullptr;
+  // fused reverse steps of small systems, allocated at their first use: the second
+  // published set, every level's contributions to the field gradient and their sums,
+  // the bond Jacobians of up to jac_levels levels
+  std::vector<void*>* allocs = nullptr;
+  double* jac = nullptr;     // [jac_levels][11][9][N]
+  int jac_levels = 0;
+  double* pub = nullptr;     // [12N]
+  double* fieldc = nullptr;  // [every + 1][12][N]
+  double* fieldp = nullptr;  // [every + 1][M][12]
 };
 
 int tape_init(Tape& t, const Dev& d, int every, int capacity, std::vector<void*>& allocs);
 int tape_start(Tape& t, const Dev& d, hipStream_t s, int64_t step);
 int tape_before_step(Tape& t, const Dev& d, hipStream_t s, int64_t step);
 int adjoint_run(Tape& t, const Dev& d, int precision, const DipWork* work, int nwork,
-                hipStream_t s, int64_t end_step, const rod_cotangent* gy, rod_gradients* gx);
+                int max_slots, const TapeSmall& small, hipStream_t s, int64_t end_step,
+                const rod_cotangent* gy, rod_gradients* gx);
 void tape_release(Tape& t);
 
 }  // namespace rodmx

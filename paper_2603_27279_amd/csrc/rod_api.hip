@@ -1525,8 +1525,14 @@ int rod_grad(rod_ctx* c, const rod_cotangent* gy, rod_gradients* gx) {
     return fail(ROD_E_NOTAPE, "no recorded steps: call rod_tape_begin, then rod_step");
   TRY(enter(c));
   const bool cut = c->d.dcut > 0.0;
+  TapeSmall small;
+  if (small_steps(c)) {
+    small.mu = c->alt + 13 * c->d.n;
+    small.muf = c->alt_muf;
+    small.many = many_steps(c) ? c->max_member : 0;
+  }
   TRY(adjoint_run(c->tape, c->d, c->desc.precision, cut ? c->adj_work : c->work,
-                  cut ? c->adj_nwork : c->nwork, c->s, c->h_step, gy, gx));
+                  cut ? c->adj_nwork : c->nwork, c->max_slots, small, c->s, c->h_step, gy, gx));
   TRY(leave(c));
   return ROD_OK;
 }

@@ -96,6 +96,26 @@ __device__ __forceinline__ void wave_sum10(double v[10], double* out) {
   }
 }
 
+// Six sums over the wave, as above.
+__device__ __forceinline__ void wave_sum6(double v[6], double* out) {
+  double h[4];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    swap32(v[2 * k], v[2 * k + 1]);
+    h[k] = v[2 * k] + v[2 * k + 1];
+  }
+  h[3] = h[2];
+  swap16(h[0], h[1]);
+  swap16(h[2], h[3]);
+  const double r0 = row_sum(h[0] + h[1]), r1 = row_sum(h[2] + h[3]);
+  const int lane = threadIdx.x & 63;
+  if ((lane & 15) == 0) {
+    const int row = lane >> 4;
+    out[((row & 1) << 1) | (row >> 1)] = r0;
+    if ((row & 1) == 0) out[4 + (row >> 1)] = r1;
+  }
+}
+
 template <int W>
 __device__ __forceinline__ Fix128 wave_sum(Fix128 v) {
   for (int o = W / 2; o > 0; o >>= 1) {
@@ -118,6 +138,13 @@ struct SmallSrc {
   long st;
   int off;
 };
+
+// Index range of the particles of i's rod within the exclusion depth of i.
+__device__ __forceinline__ void excluded_range(const Dev& d, int i, int& lo, int& hi) {
+  const int rod = d.rod[i], b = d.rod_off[rod], e = d.rod_off[rod + 1];
+  lo = i - b > d.depth ? i - d.depth : b;
+  hi = e - 1 - i > d.depth ? i + d.depth : e - 1;
+}
 
 // What a wave finds for one target: the ten dipole sums of pair_acc and, with
 // contact, its force and torque.

@@ -19,8 +19,9 @@ constexpr int STEPS_MAX = 32;  // particles of a member that k_steps can serve
 
 hipError_t launch_step(const Dev& d, int precision, const StepOut& o, hipStream_t s);
 // n steps from level lvl0 for every member, each of at most max_member <= STEPS_MAX
-// particles; not for Hertz-Mindlin contact.
+// particles; not for Hertz-Mindlin contact. With rec every level is recorded there
+// and the state is left alone.
 hipError_t launch_steps(const Dev& d, int precision, int max_member, long long lvl0, int n,
-                        hipStream_t s);
+                        hipStream_t s, double* rec = nullptr, long rec_stride = 0);
 
 }  // namespace rodmx
