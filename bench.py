@@ -310,15 +310,13 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E (vendor figure)
 #     ids (221 in); x v q w, m in FP64 and FP32 (140 out). With contact lists
 #     (these systems) the cell-list entry (key, slot, count: 40 more) is written
 #     only at list rebuilds, by the contact launch
-#   kick (per particle): bond outputs of its bond (72), dipole slots (24 each on
-#     the mixed path, 48 in FP64), contact force, state and constants (318 + slots
-#     in); F T x v w q, m twice (188 out; the cell-list entry as for pre)
+#   bond and kick in one pass, as batched steps of these systems run (per
+#     particle): x v q w (104), m_body (24), reference vector and length (32),
+#     contact force (24), masses and inertias (32), rod and member ids, flags and
+#     boundary condition (10) in; x v q w (104) out
 BYTES = {"bond": 165.0, "bond_damped": 269.0, "contact": 52.0, "contact_hm": 128.0,
-         "contact_hm_per_contact": 56.0, "dipole_cutoff": 100.0, "pre": 361.0}
-
-
-def kick_bytes(slots, slot_bytes=24.0):
-    return 318.0 + slot_bytes * slots + 188.0
+         "contact_hm_per_contact": 56.0, "dipole_cutoff": 100.0, "pre": 361.0,
+         "bond_kick": 330.0}
 
 
 def hbm_microbench(sizes, steps=10):
@@ -367,7 +365,7 @@ def hbm_microbench(sizes, steps=10):
         sim.step(steps + 1)
         kt = sim.kernel_times()
         sim.timing(False)
-        res["kick"] = entry(1e3 * kt["kick"][0] / kt["kick"][1], n, kick_bytes(0))
+        res["kick"] = entry(1e3 * kt["kick"][0] / kt["kick"][1], n, BYTES["bond_kick"])
         sim.free()
         # the bond kernel again with bond damping on every rod
         wd = dict(w, bond_damping=np.tile([0.1, 0.1, 0.1, 0.1], (R, 1)))

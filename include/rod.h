@@ -315,7 +315,10 @@ enum {
   ROD_KERNEL_CONTACT = 3, /* contact (cell list, or candidate lists) */
   ROD_KERNEL_POST = 4,    /* force gather, Zeeman, damping, second half-kick */
   ROD_KERNEL_FORCES = 5,  /* dipole, bond and (below 65536 particles) contact in one launch */
-  ROD_KERNEL_KICK = 6,    /* post of one step fused with pre of the next */
+  ROD_KERNEL_KICK = 6,    /* post of one step fused with pre of the next; with the bonds too
+                             (and then no ROD_KERNEL_FORCES launch) in batched steps of
+                             systems of 65536 particles or more without an all-pairs dipole
+                             sum, and of any size with a dipole cutoff */
   ROD_KERNEL_CELLS = 7,   /* cell-list fill before the contact launch when stepping with
                              candidate lists (empty unless the lists are rebuilt) */
   ROD_KERNEL_EWALD_REAL = 8, /* the Ewald sum's real-space walk alone (with a box; its time is
@@ -351,7 +354,10 @@ int rod_autotune(rod_ctx* c, const char* cache_path, int32_t force, char* report
  * closing half-kick and the next step's opening half-kick, drift and rotation
  * share one launch. In the small-member dipole layout a whole step is one
  * launch, and members of at most 32 particles (without Hertz-Mindlin contact)
- * take many steps per launch, whatever graph_steps says.
+ * take many steps per launch, whatever graph_steps says. Without an all-pairs
+ * dipole sum, large systems (and all with a dipole cutoff) evaluate the bonds in
+ * the fused half-kick launch; their candidate lists then outlive a call (each call
+ * checks every position against the last build's first).
  * ROD_LAUNCH_SEPARATE: as batched, with the three force terms launched as
  * separate kernels and no kick fusion (per-term timing).
  * ROD_LAUNCH_PER_ROD: the plain per-rod loop, every kernel launched once per

@@ -29,6 +29,33 @@ struct BondDamp {
   double idt;
 };
 
+// The rate terms in FP64, rounded one operation at a time: the branches around them
+// would otherwise leave it to each kernel's block structure whether a product
+// contracts with the sum behind the branch, and launch forms would differ in the last
+// bit. (In FP32 the conversions between the products and the sums settle it.)
+__device__ __forceinline__ double damped_shear(const BondDamp& dm, double Ks, double g, double gamma,
+                                               double sigma) {
+#pragma clang fp contract(off)
+  double ks = Ks * g;
+  if (dm.rates && sigma > 0.0) ks = ks + dm.gs * ((gamma - dm.hprev[0]) * dm.idt) / sigma;
+  return ks;
+}
+__device__ __forceinline__ V3<double> damped_bend(const BondDamp& dm, double Kb, double Kt, double fac,
+                                                  V3<double> bv, double psi) {
+#pragma clang fp contract(off)
+  const double th[3] = {fac * bv.x, fac * bv.y, fac * bv.z};
+  V3<double> t{Kb * fac * bv.x, Kb * fac * bv.y, Kb * fac * bv.z + Kt * psi};
+  if (dm.rates) {
+    const double twopi = 6.28318530717958647692;
+    double dpsi = psi - dm.hprev[1];
+    dpsi -= twopi * rint(dpsi / twopi);
+    t.x = t.x + dm.gb * (th[0] - dm.hprev[2]) * dm.idt;
+    t.y = t.y + dm.gb * (th[1] - dm.hprev[3]) * dm.idt;
+    t.z = t.z + (dm.gb * (th[2] - dm.hprev[4]) * dm.idt + dm.gt * dpsi * dm.idt);
+  }
+  return t;
+}
+
 template <class H, class R, bool DAMP = false>
 __device__ __forceinline__ void bond_one(V3<H> x1, V3<H> x2, Q4<H> q1, Q4<H> q2, V3<double> rref,
                                          double r0, const double* __restrict__ K4, V3<H>& Fo,
@@ -74,7 +101,8 @@ __device__ __forceinline__ void bond_one(V3<H> x1, V3<H> x2, Q4<H> q1, Q4<H> q2,
     const V3<H> vc = qrot_inv(qc, V3<H>{dm->dv.x, dm->dv.y, dm->dv.z});
     const H frad = __builtin_fma(dm->gr, dot(vc, rhat), Kr * dr);
     R ks = R(Ks) * g;
-    if (dm->rates && sigma > R(0))
+    if constexpr (sizeof(R) == 8) ks = damped_shear(*dm, Ks, g, gamma, sigma);
+    else if (dm->rates && sigma > R(0))
       ks = ks + R(dm->gs) * (R)(((double)gamma - dm->hprev[0]) * dm->idt) / sigma;
     f = (R)frad * rh + (rR * ks) * cross(c, rh);
     ts = (R(0.5) * rR * rR * ks) * c;
@@ -100,7 +128,9 @@ __device__ __forceinline__ void bond_one(V3<H> x1, V3<H> x2, Q4<H> q1, Q4<H> q2,
     // twist and bend: + g_t psi-dot (the change taken modulo 2 pi) and
     // + g_b theta-dot per component in C'
     const double th[3] = {(double)(fac * bv.x), (double)(fac * bv.y), (double)(fac * bv.z)};
-    if (dm->rates) {
+    if constexpr (sizeof(R) == 8) {
+      tbt = damped_bend(*dm, Kb, Kt, fac, bv, psi);
+    } else if (dm->rates) {
       const double twopi = 6.28318530717958647692;
       double dpsi = (double)psi - dm->hprev[1];
       dpsi -= twopi * rint(dpsi / twopi);

@@ -231,6 +231,7 @@ __device__ __forceinline__ void contact_listed(const Dev& d, long blk, bool buil
         force(xj);
       });
       d.nbr_cnt[i] = nc <= NBR_CAP ? nc : -1;
+      if (nc > NBR_CAP) atomicOr(&d.rebuild[2], 1u);
       st3(d.xb, N, i, xi);
     } else {
       for_cell_candidates(d, tab, xi, mem, [&](int j, int rj, V3<double> xj) {
@@ -375,6 +376,7 @@ __device__ __forceinline__ void contact_hm_thread(const Dev& d, long blk, bool b
     });
     if (mk) {
       d.nbr_cnt[i] = nc <= NBR_CAP ? nc : -1;
+      if (nc > NBR_CAP) atomicOr(&d.rebuild[2], 1u);
       st3(d.xb, N, i, xi);
     }
   }

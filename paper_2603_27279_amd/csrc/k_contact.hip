@@ -86,6 +86,13 @@ hipError_t launch_contact(const Dev& d, int want_energy, int build, hipStream_t 
   return hipGetLastError();
 }
 
+hipError_t launch_contact_lists(const Dev& d, hipStream_t s, const hipEvent_t* ev) {
+  const dim3 g((unsigned)((d.n + 255) / 256));
+  if (d.hm) launch_k(ev, k_contact_hm, g, dim3(256), s, d, 0);
+  else launch_k(ev, k_contact_l, g, dim3(256), s, d, 0);
+  return hipGetLastError();
+}
+
 hipError_t launch_contact_pairs(const Dev& d, int* pairs, int cap, int* count, hipStream_t s) {
   hipLaunchKernelGGL(k_contact_pairs, dim3(contact_lane_blocks(d)), dim3(256), 0, s, d, pairs, cap,
                      count);

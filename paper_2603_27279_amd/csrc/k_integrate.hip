@@ -35,9 +35,19 @@ constexpr int CELL_INSERT_WGS = 1024;
 constexpr int CELL_INSERT_ILP = 4;
 __global__ __launch_bounds__(256) void k_cell_insert(Dev d, int build) {
   const long long lvl = d.step[d.lc];
-  if (!build && d.rebuild[lvl & 1] == 0u) return;  // the lists stay
   const long N = d.n;
   const long G = (long)gridDim.x * blockDim.x;
+  if (d.cell_lvl[(lvl - 1) & 1] == lvl - 1) {  // the table filled a step ago is done with
+    const CellTab old = cell_tab(d, lvl - 1);
+    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += G) old.cnt[d.key[i]] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *old.ovf_cnt = 0;
+  }
+  const bool stale = build || d.rebuild[lvl & 1] != 0u;
+  if (!stale && d.rebuild[2] == 0u) return;  // the lists stay, and hold every candidate
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    d.cell_lvl[lvl & 1] = lvl;
+    if (stale) d.rebuild[2] = 0u;  // (the build of this level sets it again; all fill either way)
+  }
   const CellTab t = cell_tab(d, lvl);
   for (long i0 = (long)blockIdx.x * blockDim.x + threadIdx.x; i0 < N; i0 += CELL_INSERT_ILP * G) {
     V3<double> x[CELL_INSERT_ILP];
@@ -82,10 +92,12 @@ __device__ __forceinline__ V3<double> pre_particle(const Dev& d, long i, int mod
   V3<double> x = ld3(sx, N, i);
   const V3<double> mb = ld3(d.mb, N, i);
   const int mem = d.mem[i], rod = d.rod[i];
+  V3<double> vh{0.0, 0.0, 0.0};  // half-step velocity
   if (mode == PRE_STEP) {
     V3<double> v = ld3(sv, N, i), w = ld3(sw, N, i);
     advance(d, i, b, lvl, x, v, q, w, ld3(sF, N, i), ld3(sT, N, i), d.minv[i], d.Iinv[i],
             d.src != nullptr || d.nx != nullptr);
+    vh = v;
   } else if (mode == PRE_PREPARE) {
     q = qnormalize(q);
     if (b != 0) {
@@ -101,6 +113,18 @@ __device__ __forceinline__ V3<double> pre_particle(const Dev& d, long i, int mod
     st4(d.q, N, i, q);
   }
   moment_and_cell(d, i, q, x, mb, mem, rod, lvl, !(d.lazy_cells && mode == PRE_STEP));
+  if (d.halo) {  // opening the fused bond and kick chain: lists still good at these positions?
+    halo_store(d, i, lvl, x, q, vh);
+    if (d.use_lists) {
+      const V3<double> m = x - ld3(d.xb, N, i);
+      const double lim = NBR_MOVE * d.skin;
+      // (positions the caller has changed count too; a NaN asks for a build)
+      const bool far = !(dot(m, m) <= lim * lim);
+      const unsigned long long who = __ballot(far);
+      if (far && __lane_id() == (unsigned)(__ffsll((long long)who) - 1))
+        atomicOr(&d.rebuild[lvl & 1], 1u);
+    }
+  }
   return x;
 }
 

@@ -28,6 +28,26 @@ __device__ __forceinline__ void cell_place(const Dev& d, const CellTab& t, long 
   d.key[i] = (int)key;
 }
 
+// Interleaved copy of position and moment for the cutoff list walk: one line per
+// partner.
+__device__ __forceinline__ void xm_store(const Dev& d, long i, V3<double> x, V3<double> m) {
+  double* p = d.xm + 8 * i;
+  p[0] = x.x; p[1] = x.y; p[2] = x.z;
+  p[3] = m.x; p[4] = m.y; p[5] = m.z; p[6] = 0.0; p[7] = 0.0;
+}
+
+// First and last particle of each block of the fused bond and kick pass, at level lvl.
+__device__ __forceinline__ void halo_store(const Dev& d, long i, long long lvl, V3<double> x,
+                                           Q4<double> q, V3<double> v) {
+  const unsigned blk = (unsigned)i / BK_OWN, r = (unsigned)i - blk * BK_OWN;
+  if (r != 0 && r != BK_OWN - 1) return;
+  const long nblk = (d.n + BK_OWN - 1) / BK_OWN;
+  double* h = d.halo + (((lvl & 1) * nblk + blk) * 2 + (r != 0 ? 1 : 0)) * 10;
+  h[0] = x.x; h[1] = x.y; h[2] = x.z;
+  h[3] = q.w; h[4] = q.x; h[5] = q.y; h[6] = q.z;
+  h[7] = v.x; h[8] = v.y; h[9] = v.z;
+}
+
 // The particle's entry in the cell list of level lvl.
 __device__ __forceinline__ void cell_insert(const Dev& d, long i, V3<double> x, int mem, int rod,
                                             long long lvl) {
@@ -46,11 +66,7 @@ __device__ __forceinline__ void moment_and_cell(const Dev& d, long i, Q4<double>
   V3<double> m = qrot(q, mb);
   st3(d.mu, N, i, m);
   if (d.muf) st3(d.muf, N, i, V3<float>{(float)m.x, (float)m.y, (float)m.z});
-  if (d.xm) {  // interleaved copy for the cutoff list walk: one line per partner
-    double* p = d.xm + 8 * i;
-    p[0] = x.x; p[1] = x.y; p[2] = x.z;
-    p[3] = m.x; p[4] = m.y; p[5] = m.z; p[6] = 0.0; p[7] = 0.0;
-  }
+  if (d.xm) xm_store(d, i, x, m);
   if (d.contact_on && insert) cell_insert(d, i, x, mem, rod, lvl);
 }
 

@@ -68,6 +68,10 @@ struct rod_ctx {
   // Second set of state planes (x, v, q, w as in a recorded state, then moments)
   // of the fused steps of small systems, or null.
   double* alt = nullptr;
+  double* halo = nullptr;  // Dev::halo of the fused bond and kick pass, or null
+  // Something other than that pass's chain may have rebuilt one of the candidate
+  // lists (or none is built yet): the chain's next call rebuilds them all.
+  bool lists_stale = true;
   float* alt_muf = nullptr;
   int plan_small = -1, plan_target = 1024;  // current dipole layout
   std::vector<int> mslots_h;        // [M] source ranges per member of the current layout
@@ -662,6 +666,7 @@ static size_t workspace_bytes(const rod_desc* d, int max_slots) {
     const DlGeo g = dl_geometry(d);
     b += 4 * (2 * (size_t)g.nb + 1 + g.nb / DL_SCAN) + (4 * 5 + sizeof(DlRec)) * N;
   }
+  if ((long)N >= CONTACT_LANES_MAX_N || dcut) b += 320 * ((N + BK_OWN - 1) / BK_OWN);  // block ends
   if (hm) b += (24 + 8 + 2 * HM_CAP * (4 + 24)) * N;                            // torque, contacts
   if (d->dipole_on && d->box[0] > 0 && d->box[1] > 0 && d->box[2] > 0) {      // Ewald
     int nc[3], K = 0, TC = 0;
@@ -708,6 +713,7 @@ static int ewald_term(rod_ctx* c, const Dev& d) {
 
 // build: rebuild the contact candidate lists of large systems this step.
 static int force_terms(rod_ctx* c, const Dev& d, int want_energy, int build) {
+  c->lists_stale = true;
   if (!want_energy && c->launch_mode == ROD_LAUNCH_BATCHED) {
     TIMED(c, ROD_KERNEL_FORCES, launch_forces, d, c->desc.precision, c->work, c->nwork, c->s);
     if (c->desc.contact_on && !contact_in_forces(d)) TRY(contact_term(c, d, 0, build));
@@ -793,8 +799,49 @@ static int enqueue_small(rod_ctx* c, int64_t n) {
   return ROD_OK;
 }
 
+// Whether rod_step takes the fused bond and kick pass (k_bond_kick.hip): batched
+// launches of a system without an all-pairs or Ewald sum that is large enough for
+// candidate lists (65,536 particles) or keeps them for a dipole cutoff. Below that
+// the force launch and the kick are short and bound by latency; beside an all-pairs
+// sum they do not count.
+static bool bond_kick_steps(const rod_ctx* c) {
+  const Dev& d = c->d;
+  return c->launch_mode == ROD_LAUNCH_BATCHED && c->halo && !d.ew_on &&
+         (!d.dipole_on || d.dcut > 0.0) && (d.use_lists || d.n >= CONTACT_LANES_MAX_N);
+}
+
+// n steps: pre, then contact (and the cutoff walk) and the fused pass per step. The
+// pre kernel asks for new lists where a particle has moved too far since the last
+// build, whoever moved it, so lists outlive a call (open_bond_kick).
+static int open_bond_kick(rod_ctx* c) {  // before the chain, outside any captured graph
+  if (!bond_kick_steps(c) || !c->d.use_lists || !c->lists_stale) return ROD_OK;
+  // every position is far from a NaN: the chain's first step rebuilds
+  HIPC(launch_fill_i32((int*)c->d.xb, 2, -1, c->s));
+  c->lists_stale = false;
+  return ROD_OK;
+}
+static int enqueue_bond_kick(rod_ctx* c, int64_t n) {
+  Dev d = c->d;
+  d.lazy_cells = 1;
+  d.far_ok = 0;
+  d.halo = c->halo;
+  TIMED(c, ROD_KERNEL_PRE, launch_pre, d, PRE_STEP, c->s);
+  for (int64_t k = 1; k <= n; ++k) {
+    if (d.contact_on) {
+      TIMED(c, ROD_KERNEL_CELLS, launch_cell_insert, d, 0, c->s);
+      TIMED(c, ROD_KERNEL_CONTACT, launch_contact_lists, d, c->s);
+    }
+    if (d.dcut > 0) TIMED(c, ROD_KERNEL_DIPOLE, launch_dipole_cut, d, 0, c->s);
+    const int kid = k < n ? ROD_KERNEL_KICK : ROD_KERNEL_POST;
+    TIMED(c, kid, launch_bond_kick, d, c->desc.precision, k == n, c->s);
+    d.lc = 3 - d.lc;
+  }
+  return ROD_OK;
+}
+
 static int enqueue_steps(rod_ctx* c, int64_t n) {
   if (n <= 0) return ROD_OK;
+  if (bond_kick_steps(c)) return enqueue_bond_kick(c, n);
   if (small_steps(c)) return enqueue_small(c, n);
   // contact by candidate lists: the particle kernels of the stepping chain leave
   // the cell list empty, and the contact launch fills it when the lists are
@@ -872,6 +919,7 @@ static int build_rod_work(rod_ctx* c) {
 
 // The plain per-rod loop: every kernel launched once per rod on that rod's particles.
 static int enqueue_step_per_rod(rod_ctx* c) {
+  c->lists_stale = true;
   const int R = c->desc.n_rods;
   auto rod_dev = [&](int r) {
     Dev dr = c->d;
@@ -1148,7 +1196,13 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   if ((rc = ewald_setup(c, dsc, mrange))) return cleanup(rc);
   if (d.use_lists &&
       ((rc = dalloc(c, &d.nbr, (size_t)NBR_CAP * N)) || (rc = dalloc(c, &d.nbr_cnt, (size_t)N)) ||
-       (rc = dalloc(c, &d.xb, 3 * (size_t)N)) || (rc = dalloc(c, &d.rebuild, 2))))
+       (rc = dalloc(c, &d.xb, 3 * (size_t)N)) || (rc = dalloc(c, &d.rebuild, 3)) ||
+       (rc = dalloc(c, &d.cell_lvl, 2))))
+    return cleanup(rc);
+  if (d.use_lists && hipMemset(d.cell_lvl, 0x80, 2 * sizeof(long long)) != hipSuccess)
+    return cleanup(fail(ROD_E_HIP, "memset failed"));  // (no level's table is filled)
+  if (((long)N >= CONTACT_LANES_MAX_N || d.dcut > 0) && !d.ew_on && (!dsc->dipole_on || d.dcut > 0) &&
+      (rc = dalloc(c, &c->halo, 40 * (size_t)((N + BK_OWN - 1) / BK_OWN))))
     return cleanup(rc);
   d.dipole_on = dsc->dipole_on != 0; d.contact_on = dsc->contact_on != 0;
   d.cT = nullptr; d.hc_cnt = nullptr; d.hc_j = nullptr; d.hc_s = nullptr;
@@ -1231,6 +1285,7 @@ int rod_step(rod_ctx* c, int64_t n) {
   if (n < 0) return fail(ROD_E_INVALID, "n_steps must be >= 0");
   if (n == 0) return ROD_OK;
   TRY(enter(c));
+  TRY(open_bond_kick(c));
   if (c->tape.active) {
     // Checkpoint every tape_every steps; whole checkpoint intervals replay a graph.
     const int every = c->tape.every;
@@ -1525,6 +1580,7 @@ int rod_grad(rod_ctx* c, const rod_cotangent* gy, rod_gradients* gx) {
     return fail(ROD_E_NOTAPE, "no recorded steps: call rod_tape_begin, then rod_step");
   TRY(enter(c));
   const bool cut = c->d.dcut > 0.0;
+  c->lists_stale = true;
   TapeSmall small;
   if (small_steps(c)) {
     small.mu = c->alt + 13 * c->d.n;

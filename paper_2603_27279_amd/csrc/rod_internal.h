@@ -68,7 +68,14 @@ struct Dev {
   int* nbr;                // [NBR_CAP][N] candidates of each particle at the last build
   int* nbr_cnt;            // [N] candidates listed, or -1 when more than NBR_CAP
   double* xb;              // [3N] positions at the last build
-  unsigned* rebuild;       // [2] per level parity: some particle moved too far since the build
+  unsigned* rebuild;       // [2] per level parity: some particle moved too far since the build;
+                           // [2] a list of the last build had more than NBR_CAP candidates (its
+                           // particle searches the cells, which are then filled every step)
+  long long* cell_lvl;     // [2] per level parity: the level for which k_cell_insert filled the table
+  // Fused bond and kick pass of large systems (k_bond_kick.hip): the first and last
+  // particle (x, q, v) of each block of BK_OWN, [2 level parities][blocks][2][10]; set
+  // only in the copy its chain launches with.
+  double* halo;
   double skin;             // list cutoff is r_c + skin
   unsigned* flags;         // [FLAG_COUNT]: [0] non-finite state, [1] a dipole list was full,
                            // [2] overflow list full,
@@ -182,6 +189,7 @@ struct Dev {
   double ibm_idt;
 };
 
+constexpr int BK_OWN = 255;                     // particles per block of the bond and kick pass
 constexpr int CELL_CAP = 8;
 constexpr int OVF_CAP = 4096;
 constexpr int NBR_CAP = 32;                     // candidates per particle list
@@ -289,6 +297,9 @@ constexpr int EW_REACH = 3;     // real-space cells of side >= rc / EW_REACH
 // build: rebuild contact candidate lists (large systems) regardless of motion.
 hipError_t launch_contact(const Dev& d, int want_energy, int build, hipStream_t s,
                           const hipEvent_t* ev = nullptr);
+// Contact from the candidate lists, at any system size, rebuilding them where the
+// level's flag asks for it.
+hipError_t launch_contact_lists(const Dev& d, hipStream_t s, const hipEvent_t* ev = nullptr);
 // Dipole, bond and contact forces of a step in one launch.
 // Whether the contact search runs inside the fused force launch (lane-parallel
 // cell search of smaller systems, either law) or in a launch of its own
@@ -307,6 +318,10 @@ hipError_t launch_post(const Dev& d, int mode, int mask, double* Fout, double* T
 // level into step[3 - lc].
 // Bo: where to write the dipole field of the gathered level (or nullptr).
 hipError_t launch_kick(const Dev& d, double* Bo, hipStream_t s, const hipEvent_t* ev = nullptr);
+// Bonds, gather, half-kicks, drift and rotation of large systems in one pass (see
+// k_bond_kick.hip); last: closes the call.
+hipError_t launch_bond_kick(const Dev& d, int precision, int last, hipStream_t s,
+                            const hipEvent_t* ev = nullptr);
 hipError_t launch_energy(const Dev& d, double* Epart, double* out, hipStream_t s);
 hipError_t launch_contact_pairs(const Dev& d, int* pairs, int cap, int* count, hipStream_t s);
 hipError_t launch_clear_cells(const Dev& d, hipStream_t s);
