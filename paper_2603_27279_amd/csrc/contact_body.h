@@ -490,9 +490,9 @@ __device__ __forceinline__ void contact_hm_lanes(const Dev& d, long blk) {
 }
 
 // Whether the lists must be rebuilt this step: asked by the host, or some
-// particle moved too far since the last build (flag of the level's parity).
+// particle moved too far since the last build (flag of the evaluation's parity).
 __device__ __forceinline__ bool lists_stale(const Dev& d, int build) {
-  return build || d.rebuild[d.step[d.lc] & 1] != 0u;
+  return build || d.rebuild[d.lc & 1] != 0u;
 }
 
 

@@ -24,6 +24,7 @@
 // repeated gives the same bits.
 #pragma once
 #include "contact_body.h"
+#include "small_body.h"
 
 namespace rodmx {
 
@@ -58,6 +59,27 @@ __device__ __forceinline__ unsigned dl_bucket(const Dev& d, int gx, int gy, int 
          dl_spread((unsigned)gy, d.dl_axis[1]) | dl_spread((unsigned)gz, d.dl_axis[2]);
 }
 
+// Bucket and counting slot of particle i (`valid`: it exists; whole waves call), and
+// its share of its block of buckets, one addition per wave and block.
+__device__ __forceinline__ void dl_bin(const Dev& d, long i, bool valid) {
+  unsigned b = 0;
+  if (valid) {
+    const double* p = static_cast<const double*>(__builtin_assume_aligned(d.xm + 8 * i, 64));
+    b = dl_bucket(d, dl_coord(p[0], d.dl_org[0], d.dl_inv), dl_coord(p[1], d.dl_org[1], d.dl_inv),
+                  dl_coord(p[2], d.dl_org[2], d.dl_inv), d.mem[i]);
+    d.dl_bkt[i] = (int)b;
+    d.dl_slot[i] = atomicAdd(&d.dl_cnt[b], 1);
+  }
+  const int blk = (int)(b / DL_SCAN);
+  unsigned long long todo = __ballot(valid);
+  while (todo != 0ull) {
+    const int lead = __ffsll((long long)todo) - 1;
+    const unsigned long long same = __ballot(valid && blk == __builtin_amdgcn_readlane(blk, lead));
+    if ((int)__lane_id() == lead) atomicAdd(&d.dl_aux[blk], __popcll(same));
+    todo &= ~same;
+  }
+}
+
 // Workgroup b of G as dealt to the XCDs in turn, renumbered so that each XCD
 // holds a contiguous range of the sorted positions.
 __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned G) {
@@ -72,11 +94,11 @@ constexpr int DL_LANES = 8;
 // over the whole system sorted position t (workgroups dealt to the XCDs in
 // contiguous ranges), over one rod's range (the per-rod loop) the rod's
 // particle i at its own position. False past the end.
-__device__ __forceinline__ bool dl_target(const Dev& d, unsigned blk, long* i, long* t) {
+__device__ __forceinline__ bool dl_target(const Dev& d, unsigned blk, unsigned blocks, long* i, long* t) {
   const long g = threadIdx.x / DL_LANES;
   const long per = blockDim.x / DL_LANES;
   if (d.i_lo == 0 && d.i_hi == d.n) {
-    *t = (long)xcd_block(blk, gridDim.x) * per + g;
+    *t = (long)xcd_block(blk, blocks) * per + g;
     if (*t >= d.n) return false;
     *i = d.dl_sorted[*t];
   } else {
@@ -100,11 +122,12 @@ constexpr int DL_BUILD_GROUPS = 256 / DL_LANES;
 // four such chunks in flight, and write the accepted ones in candidate order
 // (each lane's place from a ballot), so the list is what one thread taking the
 // candidates in that order would write.
-__device__ __forceinline__ void dipole_list_build(const Dev& d, unsigned blk, DlCells* cells) {
+__device__ __forceinline__ void dipole_list_build(const Dev& d, unsigned blk, unsigned blocks,
+                                                  DlCells* cells) {
   constexpr int CH = 4;  // chunks of eight candidates in flight
   const long N = d.n;
   long i, t;
-  const bool live = dl_target(d, blk, &i, &t);  // whole lane groups agree
+  const bool live = dl_target(d, blk, blocks, &i, &t);  // whole lane groups agree
   if (!live) return;
   const int s = threadIdx.x % DL_LANES;
   DlCells& cl = cells[threadIdx.x / DL_LANES];
@@ -190,76 +213,104 @@ __device__ __forceinline__ void dipole_list_build(const Dev& d, unsigned blk, Dl
 }
 
 // Dipole force and field of one particle from its list, written to slot 0 of
-// the FP64 partial sums (the only slot in this mode). W lanes per particle:
-// lane s takes entries s, s + W, s + 2W, ... in order with U partners' gathers
-// in flight; the W partial sums are added by a fixed xor tree.
-constexpr int DL_WALK_LANES = 8;
-constexpr int DL_WALK_FLIGHT = 2;
-__device__ __forceinline__ void dipole_list_walk(const Dev& d, unsigned blk) {
-  constexpr int W = DL_WALK_LANES, U = DL_WALK_FLIGHT;
+// the FP64 partial sums (the only slot in this mode). W lanes per particle: lane s
+// takes entries s, s + W, s + 2W, ... in order; the W partial sums are added by a
+// fixed xor tree.
+//
+// The walk is bound by the gathers of its partners' records. One lane fetching its
+// own partner takes three 16-byte loads at 64 distinct lines each, and the texture
+// addresser handles a line per clock. Here four lanes fetch one 64-byte record
+// together (a line each four lanes, four loads for the wave's 64 partners) into
+// registers a round ahead, pass it through a wave's 4 KiB of LDS and read back
+// their own; the quarters of a record are rotated by its number so that the eight
+// lanes of a read phase fall on all banks. 262,144 particles at cutoff 3 (38 entries
+// each): 58 -> 50 us with four lanes per
+// particle (eight 55, sixteen 84, two 49).
+constexpr int DL_WALK_LANES = 4;
+struct DlStage { double2 quarter[64 * 4]; };  // one wave's records of a round
+__device__ __forceinline__ void dipole_list_walk(const Dev& d, unsigned blk, DlStage* stages) {
+  constexpr int W = DL_WALK_LANES;
   const long N = d.n;
+  const int lane = threadIdx.x & 63;
+  DlStage& st = stages[threadIdx.x >> 6];
   long i, t;
+  bool live;
   {
     const long g = threadIdx.x / W, per = blockDim.x / W;
     if (d.i_lo == 0 && d.i_hi == N) {
       t = (long)xcd_block(blk, gridDim.x) * per + g;
-      if (t >= N) return;
+      live = t < N;
+      if (!live) t = N - 1;
       i = d.dl_sorted[t];
     } else {
       i = d.i_lo + (long)blk * per + g;
-      if (i >= d.i_hi) return;
+      live = i < d.i_hi;
+      if (!live) i = d.i_lo;
       t = d.dl_pos[i];
     }
   }
   const int s = threadIdx.x % W;
   const double* own = static_cast<const double*>(__builtin_assume_aligned(d.xm + 8 * i, 64));
   const V3<double> xi{own[0], own[1], own[2]}, mi{own[3], own[4], own[5]};
-  const double rd2 = d.dcut * d.dcut, C = d.C;
-  V3<double> F{0.0, 0.0, 0.0}, B{0.0, 0.0, 0.0};
-  // partner j's position and moment from the interleaved copy (one line,
-  // three 16-byte loads)
-  auto partner = [&](int j, V3<double>& xj, V3<double>& mj) {
-    const double2* p = reinterpret_cast<const double2*>(d.xm + 8 * (long)j);
-    const double2 a = p[0], b = p[1], c = p[2];
-    xj = V3<double>{a.x, a.y, b.x};
-    mj = V3<double>{b.y, c.x, c.y};
-  };
+  const double rd2 = d.dcut * d.dcut;
+  Acc<double> A{0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   auto pair = [&](V3<double> xj, V3<double> mj) {
     const double r2 = r2_exact(xi, xj);
     if (!(r2 < rd2)) return;
     const V3<double> r = xi - xj;
-    const double rinv = rsqrt_nr(r2);  // hardware estimate, two Newton steps
-    const double rinv3 = rinv * rinv * rinv, rinv5 = rinv3 * rinv * rinv;
-    const double a = dot(mi, r), b = dot(mj, r), cmm = dot(mi, mj);
-    F = F + (3.0 * C * rinv5) * ((cmm * r + b * mi + a * mj) - (5.0 * a * b * rinv * rinv) * r);
-    B = B + (3.0 * C * b * rinv5) * r - (C * rinv3) * mj;
+    pair_acc(r.x, r.y, r.z, mj.x, mj.y, mj.z, mi.x, mi.y, mi.z, rsqrt_nr(r2), -5.0, A);
   };
-  const int nc = d.dnbr_cnt[t];
-  int k = s;
-  for (; k + (U - 1) * W < nc; k += U * W) {
-    int j[U];
-    V3<double> xj[U], mj[U];
+  const int nc = live ? d.dnbr_cnt[t] : 0;
+  int most = nc;  // of the wave's particles
 #pragma unroll
-    for (int u = 0; u < U; ++u) j[u] = d.dnbr[(long)(k + u * W) * N + t];
-#pragma unroll
-    for (int u = 0; u < U; ++u) partner(j[u], xj[u], mj[u]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) pair(xj[u], mj[u]);
+  for (int o = W; o < 64; o <<= 1) most = max(most, __shfl_xor(most, o, 64));
+  // Lane l fetches quarter (l & 3) ^ f of the records of partners 16 m + l / 4, m =
+  // 0 .. 3, f the record's rotation; entry k of the round is the lane's own partner.
+  // Entries past the end of a list are read too (they hold older particles, or 0), so
+  // that no load waits for the count.
+  const int rec = lane >> 2, quarter = (lane & 3) ^ ((rec >> 1) & 3);
+  auto entry = [&](int k) { return d.dnbr[(long)(k < DNBR_CAP ? k : s) * N + t]; };
+  auto fetch = [&](int j, int m) {
+    const long p = __shfl(j, 16 * m + rec, 64);
+    double2 v{0.0, 0.0};
+    if (quarter < 3) v = reinterpret_cast<const double2*>(d.xm + 8 * p)[quarter];
+    return v;
+  };
+  const int first = entry(s);
+  int next = entry(s + W), after = entry(s + 2 * W);
+  double2 v0 = fetch(first, 0), v1 = fetch(first, 1), v2 = fetch(first, 2), v3 = fetch(first, 3);
+  for (int k0 = 0; k0 < most; k0 += W) {
+    st.quarter[lane] = v0;
+    st.quarter[64 + lane] = v1;
+    st.quarter[128 + lane] = v2;
+    st.quarter[192 + lane] = v3;
+    if (k0 + W < most) {
+      v0 = fetch(next, 0);
+      v1 = fetch(next, 1);
+      v2 = fetch(next, 2);
+      v3 = fetch(next, 3);
+      next = after;
+      after = entry(k0 + 3 * W + s);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // LDS is the wave's own
+    __builtin_amdgcn_wave_barrier();
+    if (k0 + s < nc) {
+      const double2* r = st.quarter + 4 * lane;
+      const int f = (lane >> 1) & 3;
+      const double2 a = r[f], b = r[1 ^ f], c = r[2 ^ f];
+      pair(V3<double>{a.x, a.y, b.x}, V3<double>{b.y, c.x, c.y});
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
-  for (; k < nc; k += W) {
-    V3<double> xj, mj;
-    partner(d.dnbr[(long)k * N + t], xj, mj);
-    pair(xj, mj);
-  }
-  double v[6] = {F.x, F.y, F.z, B.x, B.y, B.z};
+  double sum[NACC] = {A.fx, A.fy, A.fz, A.fm, A.bsx, A.bsy, A.bsz, A.bmx, A.bmy, A.bmz}, w[6];
+  write_slot(w, 1, 0, d.C, sum, mi.x, mi.y, mi.z);
 #pragma unroll
-  for (int o = W / 2; o > 0; o >>= 1)
-#pragma unroll
-    for (int c = 0; c < 6; ++c) v[c] += __shfl_xor(v[c], o, 64);
-  if (s == 0) {
+  for (int c = 0; c < 6; ++c) w[c] = group_sum<W>(w[c]);
+  if (s == 0 && live) {
     double* p = d.dpart;
 #pragma unroll
-    for (int c = 0; c < 6; ++c) p[c * N + i] = v[c];
+    for (int c = 0; c < 6; ++c) p[c * N + i] = w[c];
   }
 }
 

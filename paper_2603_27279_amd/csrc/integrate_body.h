@@ -57,11 +57,12 @@ __device__ __forceinline__ void advance_particle(const Dev& d, int b, long long 
 // lvl: half-kick, drift and quaternion update of free particles; the imposed
 // rotation of driven ones. The result goes to the planes of d.nx when set,
 // else in place; states of particles that do not move are written only when
-// `copy_still` is set (out-of-place step).
+// `copy_still` is set (out-of-place step). A particle too far from its place at the
+// last list build sets rebuild[flag], the entry of the coming force evaluation.
 __device__ __forceinline__ void advance(const Dev& d, long i, int b, long long lvl, V3<double>& x,
                                         V3<double>& v, Q4<double>& q, V3<double>& w,
                                         V3<double> F, V3<double> T, double minv, double Iinv,
-                                        bool copy_still) {
+                                        bool copy_still, int flag) {
   const long N = d.n;
   // output planes: those of the next recorded state, or in place
   double* const xo = d.nx ? d.nx : d.x;
@@ -76,7 +77,7 @@ __device__ __forceinline__ void advance(const Dev& d, long i, int b, long long l
       const bool far = dot(m, m) > lim * lim;
       const unsigned long long who = __ballot(far);  // one atomic per wave
       if (far && __lane_id() == (unsigned)(__ffsll((long long)who) - 1))
-        atomicOr(&d.rebuild[lvl & 1], 1u);
+        atomicOr(&d.rebuild[flag], 1u);
     }
     st3(vo, N, i, v);
     st3(xo, N, i, x);

@@ -113,7 +113,10 @@ __global__ __launch_bounds__(256) void k_bond_kick(Dev d, int last) {
   if (blk == 0 && t == 0) {
     if (last) d.step[0] = L;
     else d.step[3 - d.lc] = L + 1;
-    if (d.use_lists) d.rebuild[L & 1] = 0u;  // (the launches that read it are over)
+    if (d.use_lists) {  // (the launches that read these are over)
+      d.rebuild[d.lc & 1] = 0u;
+      d.cell_dirty[(d.lc & 1) ^ 1] = 0;
+    }
   }
   if (!own) return;
   const Bonds bd{bF, bTs, bTb, ld3(sh, 256, (long)t - 1), ld3(sh + 3 * 256, 256, (long)t - 1),
@@ -123,14 +126,14 @@ __global__ __launch_bounds__(256) void k_bond_kick(Dev d, int last) {
   gather_sum<HM>(d, i, ROD_TERM_ALL, field_row(d, L, p.mem), p, bd, mass, inertia, Fd, Bd, cF, cT, F, T);
   kick(d, i, F, T, p, last, last);
   if (last) {
-    if (d.contact_on && d.use_lists && d.cell_lvl[L & 1] == L) {  // leave the cell list empty
+    if (d.contact_on && d.use_lists && d.cell_dirty[d.lc & 1] != 0) {  // leave the cell list empty
       const CellTab tab = cell_tab(d, L);
       tab.cnt[d.key[i]] = 0;
       if (i == 0) *tab.ovf_cnt = 0;
     }
     return;
   }
-  advance(d, i, p.b, L + 1, p.x, p.v, p.q, p.w, F, T, p.minv, p.Iinv, false);
+  advance(d, i, p.b, L + 1, p.x, p.v, p.q, p.w, F, T, p.minv, p.Iinv, false, (d.lc & 1) ^ 1);
   halo_store(d, i, L + 1, p.x, p.q, p.v);
   if (d.xm) xm_store(d, i, p.x, qrot(p.q, p.mb));
 }

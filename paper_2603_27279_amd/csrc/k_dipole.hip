@@ -5,6 +5,8 @@
 #include "dipole_list.h"
 #include "particle_body.h"
 
+#include <algorithm>
+
 namespace rodmx {
 
 template <class R>
@@ -69,17 +71,11 @@ hipError_t launch_dipole(const Dev& d, int precision, const DipWork* work, int n
 // decision is the same for every thread: the flag is written by the previous
 // step's kernels).
 
-// Each particle's bucket and counting slot.
+// Each particle's bucket and counting slot, and the particles per block of buckets.
 __global__ __launch_bounds__(256) void k_dl_bin(Dev d, int build) {
   if (!lists_stale(d, build)) return;
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d.n) return;
-  const double* p = static_cast<const double*>(__builtin_assume_aligned(d.xm + 8 * i, 64));
-  const unsigned b = dl_bucket(d, dl_coord(p[0], d.dl_org[0], d.dl_inv),
-                               dl_coord(p[1], d.dl_org[1], d.dl_inv),
-                               dl_coord(p[2], d.dl_org[2], d.dl_inv), d.mem[i]);
-  d.dl_bkt[i] = (int)b;
-  d.dl_slot[i] = atomicAdd(&d.dl_cnt[b], 1);
+  dl_bin(d, i, i < d.n);
 }
 
 // Sum over the 256 threads of a workgroup, returned to every thread.
@@ -89,18 +85,6 @@ __device__ __forceinline__ int dl_block_sum(int v, int* sh) {
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
   return sh[0] + sh[1] + sh[2] + sh[3];
-}
-
-// Particles in each block of DL_SCAN buckets (eight buckets per thread).
-__global__ __launch_bounds__(256) void k_dl_bsum(Dev d, int build) {
-  if (!lists_stale(d, build)) return;
-  __shared__ int sh[4];
-  const int* c = d.dl_cnt + (long)blockIdx.x * DL_SCAN + 8 * threadIdx.x;
-  int s = 0;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) s += c[k];
-  s = dl_block_sum(s, sh);
-  if (threadIdx.x == 0) d.dl_aux[blockIdx.x] = s;
 }
 
 // First sorted position of every bucket: the particles of the blocks before
@@ -136,9 +120,9 @@ __global__ __launch_bounds__(256) void k_dl_start(Dev d, int build) {
 // Particles grouped by bucket, in the arbitrary order of the counting slots.
 __global__ __launch_bounds__(256) void k_dl_scatter(Dev d, int build) {
   if (!lists_stale(d, build)) return;
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d.n) return;
-  d.dl_tmp[d.dl_start[d.dl_bkt[i]] + d.dl_slot[i]] = (int)i;
+  const long G = (long)gridDim.x * blockDim.x;
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < d.n; i += G)
+    d.dl_tmp[d.dl_start[d.dl_bkt[i]] + d.dl_slot[i]] = (int)i;
 }
 
 // Each bucket's particles in ascending index: a particle's place is the number
@@ -146,28 +130,31 @@ __global__ __launch_bounds__(256) void k_dl_scatter(Dev d, int build) {
 // inverse and each sorted position's record.
 __global__ __launch_bounds__(256) void k_dl_rank(Dev d, int build) {
   if (!lists_stale(d, build)) return;
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d.n) return;
-  const int b = d.dl_bkt[i];
-  const int lo = d.dl_start[b], hi = d.dl_start[b + 1];
-  int r = 0;
-  for (int q = lo; q < hi; ++q) r += d.dl_tmp[q] < (int)i;
-  const int t = lo + r;
-  d.dl_sorted[t] = (int)i;
-  d.dl_pos[i] = t;
-  const double* p = static_cast<const double*>(__builtin_assume_aligned(d.xm + 8 * i, 64));
-  DlRec e;
-  e.x = p[0]; e.y = p[1]; e.z = p[2];
-  e.i = (int)i;
-  e.tag = dl_tag(d, dl_coord(p[0], d.dl_org[0], d.dl_inv), dl_coord(p[1], d.dl_org[1], d.dl_inv),
-                 dl_coord(p[2], d.dl_org[2], d.dl_inv));
-  d.dl_rec[t] = e;
+  const long G = (long)gridDim.x * blockDim.x, first = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  for (long k = first; k < d.dl_nb / DL_SCAN; k += G)
+    d.dl_aux[k] = 0;  // (its sums have been used) for the next rebuild
+  for (long i = first; i < d.n; i += G) {
+    const int b = d.dl_bkt[i];
+    const int lo = d.dl_start[b], hi = d.dl_start[b + 1];
+    int r = 0;
+    for (int q = lo; q < hi; ++q) r += d.dl_tmp[q] < (int)i;
+    const int t = lo + r;
+    d.dl_sorted[t] = (int)i;
+    d.dl_pos[i] = t;
+    const double* p = static_cast<const double*>(__builtin_assume_aligned(d.xm + 8 * i, 64));
+    DlRec e;
+    e.x = p[0]; e.y = p[1]; e.z = p[2];
+    e.i = (int)i;
+    e.tag = dl_tag(d, dl_coord(p[0], d.dl_org[0], d.dl_inv), dl_coord(p[1], d.dl_org[1], d.dl_inv),
+                   dl_coord(p[2], d.dl_org[2], d.dl_inv));
+    d.dl_rec[t] = e;
+  }
 }
 
-hipError_t launch_dipole_sort(const Dev& d, int build, hipStream_t s) {
-  const unsigned gp = (unsigned)((d.n + 255) / 256), gb = (unsigned)(d.dl_nb / DL_SCAN);
-  hipLaunchKernelGGL(k_dl_bin, dim3(gp), dim3(256), 0, s, d, build);
-  hipLaunchKernelGGL(k_dl_bsum, dim3(gb), dim3(256), 0, s, d, build);
+hipError_t launch_dipole_sort(const Dev& d, int build, hipStream_t s, bool binned) {
+  const unsigned gp = gated_blocks((d.n + 255) / 256), gb = (unsigned)(d.dl_nb / DL_SCAN);
+  if (!binned)
+    hipLaunchKernelGGL(k_dl_bin, dim3((unsigned)((d.n + 255) / 256)), dim3(256), 0, s, d, build);
   hipLaunchKernelGGL(k_dl_start, dim3(gb), dim3(256), 0, s, d, build);
   hipLaunchKernelGGL(k_dl_scatter, dim3(gp), dim3(256), 0, s, d, build);
   hipLaunchKernelGGL(k_dl_rank, dim3(gp), dim3(256), 0, s, d, build);
@@ -177,9 +164,40 @@ hipError_t launch_dipole_sort(const Dev& d, int build, hipStream_t s) {
 __global__ __launch_bounds__(256) void k_dipole_lb(Dev d, int build) {
   if (!lists_stale(d, build)) return;
   __shared__ DlCells cells[DL_BUILD_GROUPS];
-  dipole_list_build(d, blockIdx.x, cells);
+  dipole_list_build(d, blockIdx.x, gridDim.x, cells);
 }
-__global__ __launch_bounds__(256) void k_dipole_l(Dev d) { dipole_list_walk(d, blockIdx.x); }
+__global__ __launch_bounds__(256, 5) void k_dipole_l(Dev d) {
+  __shared__ DlStage stages[4];
+  dipole_list_walk(d, blockIdx.x, stages);
+}
+
+// Contact (Hookean) from its candidate lists and the build of the dipole lists, side
+// by side in one launch: most steps build nothing, and an idle launch costs as much
+// as the contact walk.
+__global__ __launch_bounds__(256) void k_contact_lb(Dev d, unsigned ncont, unsigned nlb) {
+  __shared__ DlCells cells[DL_BUILD_GROUPS];
+  const bool stale = lists_stale(d, 0);
+  if (blockIdx.x < ncont) contact_listed(d, blockIdx.x, stale);
+  else if (stale)  // (a multiple of the 8 XCDs, so that a workgroup's ranges stay on its own)
+    for (unsigned b = blockIdx.x - ncont; b < nlb; b += gridDim.x - ncont) dipole_list_build(d, b, nlb, cells);
+}
+
+hipError_t launch_cut_step(const Dev& d, hipStream_t s) {
+  hipError_t e = launch_dipole_sort(d, 0, s, true);
+  if (e != hipSuccess) return e;
+  const unsigned ncont = (unsigned)((d.n + 255) / 256);
+  const long pb = 256 / DL_LANES, pw = 256 / DL_WALK_LANES;
+  const unsigned nlb = (unsigned)((d.n + pb - 1) / pb);
+  if (d.hm) {
+    if ((e = launch_contact_lists(d, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_dipole_lb, dim3(nlb), dim3(256), 0, s, d, 0);
+  } else {
+    hipLaunchKernelGGL(k_contact_lb, dim3(ncont + std::min(nlb, 2048u)), dim3(256), 0, s, d, ncont,
+                       nlb);
+  }
+  hipLaunchKernelGGL(k_dipole_l, dim3((unsigned)((d.n + pw - 1) / pw)), dim3(256), 0, s, d);
+  return hipGetLastError();
+}
 
 // Over the whole system: the sort and the list build (at a rebuild), then the
 // walk; over one rod's range (per-rod loop) the build and the walk, the sort

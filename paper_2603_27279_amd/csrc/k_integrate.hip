@@ -7,6 +7,7 @@
 #include "rod_internal.h"
 #include "rod_math.h"
 #include "particle_body.h"
+#include "dipole_list.h"
 #include "integrate_body.h"  // last: contraction within expressions from here on
 
 namespace rodmx {
@@ -28,25 +29,30 @@ __global__ __launch_bounds__(256) void k_pre(Dev d, int mode) {
 // Cell-list entries of the level being evaluated, when its contact lists are
 // rebuilt (lazy_cells: the particle kernels left the list empty). Most steps
 // keep their lists, and then every workgroup only reads the flag: the grid is
-// capped at CELL_INSERT_WGS workgroups (a few per compute unit), each thread
+// capped (gated_blocks), each thread
 // striding over the particles CELL_INSERT_ILP at a time, so that their loads
 // and slot claims are in flight together.
-constexpr int CELL_INSERT_WGS = 1024;
 constexpr int CELL_INSERT_ILP = 4;
 __global__ __launch_bounds__(256) void k_cell_insert(Dev d, int build) {
+  // three flags that nothing else has to be loaded for: an idle launch is their latency
+  const bool stale = build || d.rebuild[d.lc & 1] != 0u, over = d.rebuild[2] != 0u;
+  const bool dirty = d.cell_dirty[(d.lc & 1) ^ 1] != 0;
+  if (!stale && !over && !dirty) return;
   const long long lvl = d.step[d.lc];
   const long N = d.n;
   const long G = (long)gridDim.x * blockDim.x;
-  if (d.cell_lvl[(lvl - 1) & 1] == lvl - 1) {  // the table filled a step ago is done with
+  if (dirty) {  // the table filled a step ago is done with
     const CellTab old = cell_tab(d, lvl - 1);
     for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += G) old.cnt[d.key[i]] = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) *old.ovf_cnt = 0;
   }
-  const bool stale = build || d.rebuild[lvl & 1] != 0u;
-  if (!stale && d.rebuild[2] == 0u) return;  // the lists stay, and hold every candidate
+  if (!stale && !over) return;  // the lists stay, and hold every candidate
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    d.cell_lvl[lvl & 1] = lvl;
+    d.cell_dirty[d.lc & 1] = 1;
     if (stale) d.rebuild[2] = 0u;  // (the build of this level sets it again; all fill either way)
+  }
+  if (stale && d.dcut > 0.0 && d.halo) {  // the cutoff sort's buckets in the same launch
+    for (long i0 = (long)blockIdx.x * blockDim.x; i0 < N; i0 += G) dl_bin(d, i0 + threadIdx.x, i0 + threadIdx.x < N);
   }
   const CellTab t = cell_tab(d, lvl);
   for (long i0 = (long)blockIdx.x * blockDim.x + threadIdx.x; i0 < N; i0 += CELL_INSERT_ILP * G) {
@@ -71,8 +77,7 @@ __global__ __launch_bounds__(256) void k_cell_insert(Dev d, int build) {
 
 hipError_t launch_cell_insert(const Dev& d, int build, hipStream_t s, const hipEvent_t* ev) {
   const long blocks = (d.n + 255) / 256;
-  launch_k(ev, k_cell_insert, dim3((unsigned)(blocks < CELL_INSERT_WGS ? blocks : CELL_INSERT_WGS)), dim3(256),
-           s, d, build);
+  launch_k(ev, k_cell_insert, dim3(gated_blocks(blocks)), dim3(256), s, d, build);
   return hipGetLastError();
 }
 
@@ -96,7 +101,7 @@ __device__ __forceinline__ V3<double> pre_particle(const Dev& d, long i, int mod
   if (mode == PRE_STEP) {
     V3<double> v = ld3(sv, N, i), w = ld3(sw, N, i);
     advance(d, i, b, lvl, x, v, q, w, ld3(sF, N, i), ld3(sT, N, i), d.minv[i], d.Iinv[i],
-            d.src != nullptr || d.nx != nullptr);
+            d.src != nullptr || d.nx != nullptr, d.lc & 1);
     vh = v;
   } else if (mode == PRE_PREPARE) {
     q = qnormalize(q);
@@ -122,7 +127,7 @@ __device__ __forceinline__ V3<double> pre_particle(const Dev& d, long i, int mod
       const bool far = !(dot(m, m) <= lim * lim);
       const unsigned long long who = __ballot(far);
       if (far && __lane_id() == (unsigned)(__ffsll((long long)who) - 1))
-        atomicOr(&d.rebuild[lvl & 1], 1u);
+        atomicOr(&d.rebuild[d.lc & 1], 1u);
     }
   }
   return x;
@@ -216,7 +221,7 @@ __global__ __launch_bounds__(256) void k_post(Dev d, int mode, int mask, double*
   if (i == 0 && (!SPLIT || threadIdx.x < 64)) {
     if (mode == POST_KICK) d.step[0] = lvl;
     *cell_tab(d, lvl).ovf_cnt = 0;  // the contact pass that used the overflow list has finished
-    if (d.use_lists) d.rebuild[lvl & 1] = 0u;  // and so has the one that read this flag
+    if (d.use_lists) d.rebuild[d.lc & 1] = 0u;  // and so has the one that read this flag
   }
   V3<double> Fd, Bd;
   if (!dipole_sums_of<SPLIT>(d, i, i < d.i_hi, mask, Fd, Bd, part)) return;
@@ -251,7 +256,7 @@ __global__ __launch_bounds__(256) void k_kick(Dev d, double* Bo) {
   if (i == 0 && (!SPLIT || threadIdx.x < 64)) {
     d.step[3 - d.lc] = L + 1;
     *cell_tab(d, L).ovf_cnt = 0;
-    if (d.use_lists) d.rebuild[L & 1] = 0u;
+    if (d.use_lists) d.rebuild[d.lc & 1] = 0u;
   }
   const bool valid = i < d.i_hi;
   V3<double> x{0.0, 0.0, 0.0};
@@ -267,7 +272,7 @@ __global__ __launch_bounds__(256) void k_kick(Dev d, double* Bo) {
     const bool apart = d.nx != nullptr;
     kick(d, i, F, T, p, apart);
     if (d.contact_on) cell_tab(d, L).cnt[key] = 0;
-    advance(d, i, p.b, L + 1, p.x, p.v, p.q, p.w, F, T, p.minv, p.Iinv, apart);
+    advance(d, i, p.b, L + 1, p.x, p.v, p.q, p.w, F, T, p.minv, p.Iinv, apart, (d.lc & 1) ^ 1);
     moment_and_cell(d, i, p.q, p.x, p.mb, p.mem, p.rod, L + 1, !d.lazy_cells);
     x = p.x;
   }

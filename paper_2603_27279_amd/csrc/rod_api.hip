@@ -828,10 +828,16 @@ static int enqueue_bond_kick(rod_ctx* c, int64_t n) {
   TIMED(c, ROD_KERNEL_PRE, launch_pre, d, PRE_STEP, c->s);
   for (int64_t k = 1; k <= n; ++k) {
     if (d.contact_on) {
+      if (c->timing) d.halo = nullptr;  // (the cutoff sort in the dipole class)
       TIMED(c, ROD_KERNEL_CELLS, launch_cell_insert, d, 0, c->s);
-      TIMED(c, ROD_KERNEL_CONTACT, launch_contact_lists, d, c->s);
+      d.halo = c->halo;
     }
-    if (d.dcut > 0) TIMED(c, ROD_KERNEL_DIPOLE, launch_dipole_cut, d, 0, c->s);
+    if (d.dcut > 0 && !c->timing) {
+      HIPC(launch_cut_step(d, c->s));
+    } else {
+      if (d.contact_on) TIMED(c, ROD_KERNEL_CONTACT, launch_contact_lists, d, c->s);
+      if (d.dcut > 0) TIMED(c, ROD_KERNEL_DIPOLE, launch_dipole_cut, d, 0, c->s);
+    }
     const int kid = k < n ? ROD_KERNEL_KICK : ROD_KERNEL_POST;
     TIMED(c, kid, launch_bond_kick, d, c->desc.precision, k == n, c->s);
     d.lc = 3 - d.lc;
@@ -1197,10 +1203,8 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   if (d.use_lists &&
       ((rc = dalloc(c, &d.nbr, (size_t)NBR_CAP * N)) || (rc = dalloc(c, &d.nbr_cnt, (size_t)N)) ||
        (rc = dalloc(c, &d.xb, 3 * (size_t)N)) || (rc = dalloc(c, &d.rebuild, 3)) ||
-       (rc = dalloc(c, &d.cell_lvl, 2))))
+       (rc = dalloc(c, &d.cell_dirty, 2))))
     return cleanup(rc);
-  if (d.use_lists && hipMemset(d.cell_lvl, 0x80, 2 * sizeof(long long)) != hipSuccess)
-    return cleanup(fail(ROD_E_HIP, "memset failed"));  // (no level's table is filled)
   if (((long)N >= CONTACT_LANES_MAX_N || d.dcut > 0) && !d.ew_on && (!dsc->dipole_on || d.dcut > 0) &&
       (rc = dalloc(c, &c->halo, 40 * (size_t)((N + BK_OWN - 1) / BK_OWN))))
     return cleanup(rc);

@@ -68,10 +68,10 @@ struct Dev {
   int* nbr;                // [NBR_CAP][N] candidates of each particle at the last build
   int* nbr_cnt;            // [N] candidates listed, or -1 when more than NBR_CAP
   double* xb;              // [3N] positions at the last build
-  unsigned* rebuild;       // [2] per level parity: some particle moved too far since the build;
+  unsigned* rebuild;       // [2] by the parity of lc: some particle moved too far since the build;
                            // [2] a list of the last build had more than NBR_CAP candidates (its
                            // particle searches the cells, which are then filled every step)
-  long long* cell_lvl;     // [2] per level parity: the level for which k_cell_insert filled the table
+  int* cell_dirty;         // [2] by the parity of lc: k_cell_insert filled that evaluation's table
   // Fused bond and kick pass of large systems (k_bond_kick.hip): the first and last
   // particle (x, q, v) of each block of BK_OWN, [2 level parities][blocks][2][10]; set
   // only in the copy its chain launches with.
@@ -137,7 +137,7 @@ struct Dev {
   int dl_mshift;
   int dl_nb;               // buckets (a power of two, a multiple of DL_SCAN)
   int* dl_cnt;             // [nb] particles per bucket (zero between rebuilds)
-  int* dl_aux;             // [nb / DL_SCAN] count of each scan block
+  int* dl_aux;             // [nb / DL_SCAN] particles per block of buckets (zero between rebuilds)
   int* dl_start;           // [nb + 1] first sorted position of each bucket
   int* dl_bkt;             // [N] bucket of each particle
   int* dl_slot;            // [N] its counting slot in the bucket
@@ -249,6 +249,12 @@ constexpr int DIP_SMALL_I = 4;
 // systems over more compute units.
 inline int particle_block(long n) { return n < 65536 ? 64 : 256; }
 
+// Workgroups of a launch that most steps leave at once, its lists being good: few
+// enough that dispatching them costs little (an idle launch of 1024 takes 4.6 us), with
+// strided threads.
+constexpr long GATED_WGS = 256;
+inline unsigned gated_blocks(long blocks) { return (unsigned)(blocks < GATED_WGS ? blocks : GATED_WGS); }
+
 // Kernel launchers (each enqueues on `s`; return the launch status).
 // Launch that, given `ev`, has the runtime stamp ev[0] and ev[1] with the
 // kernel's own start and end (timing mode); a plain launch otherwise.
@@ -280,7 +286,11 @@ hipError_t launch_dipole_cut(const Dev& d, int build, hipStream_t s,
                              const hipEvent_t* ev = nullptr);
 // The cutoff sort alone (when the lists are stale or `build`), over the whole
 // system: launched once before the per-rod loop's list walks.
-hipError_t launch_dipole_sort(const Dev& d, int build, hipStream_t s);
+// binned: the particles are already in their buckets (launch_cell_insert).
+hipError_t launch_dipole_sort(const Dev& d, int build, hipStream_t s, bool binned = false);
+// A step's contact and cutoff dipoles after launch_cell_insert with d.halo set (the
+// chain of the fused bond and kick pass).
+hipError_t launch_cut_step(const Dev& d, hipStream_t s);
 // Boxes of the 64-position chunks of the spatial order (d.dperm) into d.sbox;
 // nothing without a spatial order.
 hipError_t launch_spatial_boxes(const Dev& d, hipStream_t s);

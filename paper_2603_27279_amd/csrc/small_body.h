@@ -42,14 +42,16 @@ constexpr int DPP_XOR1 = 0xb1, DPP_XOR2 = 0x4e, DPP_XOR3 = 0x1b;  // quad permut
 constexpr int DPP_ROR8 = 0x128;                                  // lane ^ 8 in a row of 16
 constexpr int DPP_HALF_MIRROR = 0x141;                           // lane ^ 7
 
-// Levels 8, 4, 2, 1 of one register.
-__device__ __forceinline__ double row_sum(double a) {
-  a += dpp<DPP_ROR8>(a);
-  a += dpp<DPP_XOR3>(dpp<DPP_HALF_MIRROR>(a));  // lane ^ 7 ^ 3 = lane ^ 4
-  a += dpp<DPP_XOR2>(a);
-  a += dpp<DPP_XOR1>(a);
+// The levels inside groups of W <= 16 lanes, of one register.
+template <int W>
+__device__ __forceinline__ double group_sum(double a) {
+  if constexpr (W >= 16) a += dpp<DPP_ROR8>(a);
+  if constexpr (W >= 8) a += dpp<DPP_XOR3>(dpp<DPP_HALF_MIRROR>(a));  // lane ^ 7 ^ 3 = lane ^ 4
+  if constexpr (W >= 4) a += dpp<DPP_XOR2>(a);
+  if constexpr (W >= 2) a += dpp<DPP_XOR1>(a);
   return a;
 }
+__device__ __forceinline__ double row_sum(double a) { return group_sum<16>(a); }
 
 // The ten sums over each group of W lanes (64, 32 or 16), written to its out[0..10)
 // (LDS) by the lanes that end up with them. A narrower group starts the tree at its
