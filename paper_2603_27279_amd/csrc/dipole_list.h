@@ -258,7 +258,7 @@ __device__ __forceinline__ void dipole_list_walk(const Dev& d, unsigned blk, DlS
     const double r2 = r2_exact(xi, xj);
     if (!(r2 < rd2)) return;
     const V3<double> r = xi - xj;
-    pair_acc(r.x, r.y, r.z, mj.x, mj.y, mj.z, mi.x, mi.y, mi.z, rsqrt_nr(r2), -5.0, A);
+    pair_acc(r.x, r.y, r.z, mj.x, mj.y, mj.z, mi.x, mi.y, mi.z, rsqrt_pair(r2), -5.0, A);
   };
   const int nc = live ? d.dnbr_cnt[t] : 0;
   int most = nc;  // of the wave's particles

@@ -208,7 +208,7 @@ __device__ __forceinline__ void ew_pair(V3<R> r, R r2, V3<R> mi, V3<R> mj, R a, 
                                         V3<R>& F, V3<R>& B) {
   R ri, ex, ec, ar2;
   if constexpr (sizeof(R) == 8) {
-    ri = rsqrt_nr(r2);  // hardware estimate, two Newton steps
+    ri = rsqrt_pair(r2);
   } else {
     ri = __builtin_amdgcn_rsqf(r2);
   }

@@ -648,6 +648,15 @@ static DlGeo dl_geometry(const rod_desc* d) {
   return g;
 }
 
+// Work items that the split dipole layout aims at unless the caller or the tuner says
+// otherwise: 1024, four per compute unit; in FP64 from 8192 particles on 4096, whose
+// last ones leave fewer units idle (carpets of 10,314 and 18,598 particles: 200 -> 185
+// and 594 -> 564 us per step; the twisted rod's 4096 particles 44.5 and 45.8). On the
+// mixed path the slots are FP32 and their number decides the rounding: it stays.
+static int default_work_items(const rod_desc* d) {
+  return d->precision == ROD_FP64 && d->n_particles >= 8192 ? 4096 : 1024;
+}
+
 static size_t workspace_bytes(const rod_desc* d, int max_slots) {
   size_t N = d->n_particles, R = d->n_rods, M = d->n_members;
   size_t cells = d->contact_on ? next_pow2(std::max<size_t>(1024, 2 * N)) : 1;
@@ -678,7 +687,7 @@ static size_t workspace_bytes(const rod_desc* d, int max_slots) {
   if (d->precision == ROD_MIXED && d->dipole_on) b += 48 * ((N + 63) / 64);  // chunk boxes
   if (d->dipole_on) b += 4 * N + 48 * ((N + 63) / 64);  // spatial order and its chunk boxes
   if (d->bond_damping) b += 8 * 4 * R + 8 * 2 * 5 * N;                       // bond damping
-  b += 8 * 18 * N + 8 * 9 * M;                                                  // energy
+  b += 8 * energy_doubles(N, M) + 8 * 9 * M;                                                  // energy
   if (!dcut && !(d->box[0] > 0)) {  // second state planes of the fused small steps
     std::vector<long> size(M, 0);
     long largest = 0;
@@ -1031,7 +1040,7 @@ const char* rod_last_error(void) { return g_err.c_str(); }
 int rod_query_workspace(const rod_desc* d, size_t* bytes) {
   TRY(validate(d));
   if (!bytes) return fail(ROD_E_INVALID, "bytes is NULL");
-  *bytes = workspace_bytes(d, 16);
+  *bytes = workspace_bytes(d, default_work_items(d) > 1024 ? 32 : 16);
   return ROD_OK;
 }
 
@@ -1141,7 +1150,7 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
       (rc = dalloc(c, &d.key, (size_t)N)) || (rc = dalloc(c, &d.ovf_list, 2 * (size_t)OVF_CAP)) ||
       (rc = dalloc(c, &d.ovf_cnt, 2)) || (rc = dalloc(c, &d.flags, FLAG_COUNT)) ||
       (rc = dalloc(c, &d.step, 3)) ||
-      (rc = dalloc(c, &c->epart, 18 * (size_t)N)) || (rc = dalloc(c, &c->eout, 9 * (size_t)M)) ||
+      (rc = dalloc(c, &c->epart, energy_doubles(N, M))) || (rc = dalloc(c, &c->eout, 9 * (size_t)M)) ||
       (rc = dalloc(c, &c->pair_count, 1)))
     return cleanup(rc);
   d.muf = dsc->precision == ROD_MIXED ? muf : nullptr;
@@ -1251,7 +1260,7 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   if (hipMemcpy(d.step, s0, sizeof(s0), hipMemcpyHostToDevice) != hipSuccess)
     return cleanup(fail(ROD_E_HIP, "upload failed"));
   c->mrange_h = mrange;
-  if ((rc = build_dipole_plan(c, -1, 1024))) return cleanup(rc);
+  if ((rc = build_dipole_plan(c, -1, default_work_items(dsc)))) return cleanup(rc);
   // descriptor host pointers are not kept
   c->desc.rod_offset = nullptr; c->desc.rod_member = nullptr; c->desc.rod_params = nullptr;
   c->desc.x_ref = nullptr; c->desc.bc = nullptr; c->desc.bond_damping = nullptr;
@@ -1384,7 +1393,7 @@ int rod_energy(rod_ctx* c, double* out, int32_t on_device) {
   TRY(enter(c));
   HIPC(launch_pre(c->d, PRE_EVAL, c->s));
   TRY(force_terms(c, 1));
-  HIPC(launch_energy(c->d, c->epart, c->eout, c->s));
+  HIPC(launch_energy(c->d, c->max_member, c->epart, c->eout, c->s));
   const size_t bytes = 9 * sizeof(double) * c->d.M;
   if (on_device) {
     HIPC(hipMemcpyAsync(out, c->eout, bytes, hipMemcpyDeviceToDevice, c->s));

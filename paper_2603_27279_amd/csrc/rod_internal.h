@@ -332,7 +332,9 @@ hipError_t launch_kick(const Dev& d, double* Bo, hipStream_t s, const hipEvent_t
 // k_bond_kick.hip); last: closes the call.
 hipError_t launch_bond_kick(const Dev& d, int precision, int last, hipStream_t s,
                             const hipEvent_t* ev = nullptr);
-hipError_t launch_energy(const Dev& d, double* Epart, double* out, hipStream_t s);
+// Energies of every member into out[M][9]; Epart holds energy_doubles(n, M).
+hipError_t launch_energy(const Dev& d, int max_member, double* Epart, double* out, hipStream_t s);
+inline size_t energy_doubles(size_t n, size_t M) { return 9 * n + 9 * (n / 256 + M + 1); }
 hipError_t launch_contact_pairs(const Dev& d, int* pairs, int cap, int* count, hipStream_t s);
 hipError_t launch_clear_cells(const Dev& d, hipStream_t s);
 // Fill p[0..n) with v.
