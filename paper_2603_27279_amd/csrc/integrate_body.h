@@ -132,7 +132,7 @@ __device__ __forceinline__ const double* field_row(const Dev& d, long long lvl, 
 // HM: the contact law is Hertz-Mindlin, whose contacts also exert a torque (a
 // template argument, so that the Hookean kernels carry no extra load). FL: the
 // immersed-boundary penalty m_p / dt_fluid (U_p - v_p) with the velocity the
-// evaluation sees, also stored to d.ibm_f (only the unfused post kernel).
+// evaluation sees, also stored to d.ibm_f.
 template <bool HM, bool FL = false>
 __device__ __forceinline__ void gather_sum(const Dev& d, long i, int mask, const double* f,
                                            const PIn& p, const Bonds& bd, double mass,

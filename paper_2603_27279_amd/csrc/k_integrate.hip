@@ -249,7 +249,9 @@ __global__ __launch_bounds__(256) void k_post(Dev d, int mode, int mask, double*
 // half-kick at level L = step[lc], then half-kick, drift, rotation, moments and
 // cell insertion for level L + 1 (written to step[3 - lc]). The cell list and
 // overflow list of level L are emptied while those of level L + 1 are filled.
-template <bool HM, bool SPLIT>
+// FL: with the immersed-boundary penalty, whose positions are put aside (d.ibm_x) for
+// the spreading in the next force launch.
+template <bool HM, bool SPLIT, bool FL>
 __global__ __launch_bounds__(256) void k_kick(Dev d, double* Bo) {
   __shared__ double part[SPLIT ? 6 * 64 * SPLIT_WAVES : 1];
   const long i = d.i_lo + (SPLIT ? (long)blockIdx.x * 64 + (threadIdx.x & 63)
@@ -268,7 +270,8 @@ __global__ __launch_bounds__(256) void k_kick(Dev d, double* Bo) {
     PIn p = load_particle(d, i);
     const int key = d.contact_on ? d.key[i] : 0;
     V3<double> F, T;
-    gather<HM>(d, i, ROD_TERM_ALL, L, Bo, p, Fd, Bd, F, T);
+    gather<HM, FL>(d, i, ROD_TERM_ALL, L, Bo, p, Fd, Bd, F, T);
+    if constexpr (FL) st3(d.ibm_x, d.n, i, p.x);
     // in place, the next half-kick overwrites v and w; out of place (a recorded
     // state) the full-step v and w stay with level L
     const bool apart = d.nx != nullptr;
@@ -378,16 +381,24 @@ hipError_t launch_post(const Dev& d, int mode, int mask, double* Fo, double* To,
   return hipGetLastError();
 }
 
+template <bool SPLIT>
+static void kick_variant(const Dev& d, double* Bo, hipStream_t s, const hipEvent_t* ev, dim3 g, dim3 b) {
+  if (d.ibm_u) {
+    if (d.hm) launch_k(ev, k_kick<true, SPLIT, true>, g, b, s, d, Bo);
+    else launch_k(ev, k_kick<false, SPLIT, true>, g, b, s, d, Bo);
+  } else if (d.hm) {
+    launch_k(ev, k_kick<true, SPLIT, false>, g, b, s, d, Bo);
+  } else {
+    launch_k(ev, k_kick<false, SPLIT, false>, g, b, s, d, Bo);
+  }
+}
+
 hipError_t launch_kick(const Dev& d, double* Bo, hipStream_t s, const hipEvent_t* ev) {
   if (particle_split(d.n)) {
-    const dim3 g(blocks_for(d.i_hi - d.i_lo, 64)), b(64 * SPLIT_WAVES);
-    if (d.hm) launch_k(ev, k_kick<true, true>, g, b, s, d, Bo);
-    else launch_k(ev, k_kick<false, true>, g, b, s, d, Bo);
+    kick_variant<true>(d, Bo, s, ev, dim3(blocks_for(d.i_hi - d.i_lo, 64)), dim3(64 * SPLIT_WAVES));
   } else {
     const int bs = particle_block(d.n);
-    const dim3 g(blocks_for(d.i_hi - d.i_lo, bs)), b(bs);
-    if (d.hm) launch_k(ev, k_kick<true, false>, g, b, s, d, Bo);
-    else launch_k(ev, k_kick<false, false>, g, b, s, d, Bo);
+    kick_variant<false>(d, Bo, s, ev, dim3(blocks_for(d.i_hi - d.i_lo, bs)), dim3(bs));
   }
   return hipGetLastError();
 }

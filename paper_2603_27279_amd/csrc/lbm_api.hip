@@ -12,6 +12,7 @@
 #include "rod.h"
 #include "lbm.h"
 #include "lbm_internal.h"
+#include "lbm_body.h"
 
 #include <hip/hip_runtime.h>
 #include <cmath>
@@ -20,35 +21,6 @@
 #include <string>
 
 namespace lbmx {
-
-// D3Q19 in the order of lbm.h (the loops over i are unrolled, so every lookup
-// is a compile-time constant).
-__device__ __forceinline__ constexpr int CX(int i) {
-  constexpr int v[19] = {0, 1, -1, 0, 0, 0, 0, 1, -1, 1, -1, 1, -1, 1, -1, 0, 0, 0, 0};
-  return v[i];
-}
-__device__ __forceinline__ constexpr int CY(int i) {
-  constexpr int v[19] = {0, 0, 0, 1, -1, 0, 0, 1, -1, -1, 1, 0, 0, 0, 0, 1, -1, 1, -1};
-  return v[i];
-}
-__device__ __forceinline__ constexpr int CZ(int i) {
-  constexpr int v[19] = {0, 0, 0, 0, 0, 1, -1, 0, 0, 0, 0, 1, -1, -1, 1, 1, -1, -1, 1};
-  return v[i];
-}
-__device__ __forceinline__ constexpr int OPP(int i) {
-  constexpr int v[19] = {0, 2, 1, 4, 3, 6, 5, 8, 7, 10, 9, 12, 11, 14, 13, 16, 15, 18, 17};
-  return v[i];
-}
-// The direction with the z component reversed (specular reflection).
-__device__ __forceinline__ constexpr int FLIPZ(int i) {
-  constexpr int v[19] = {0, 1, 2, 3, 4, 6, 5, 7, 8, 9, 10, 13, 14, 11, 12, 17, 18, 15, 16};
-  return v[i];
-}
-
-__device__ __forceinline__ double weight(int i) {
-  return i == 0 ? 1.0 / 3.0 : (i < 7 ? 1.0 / 18.0 : 1.0 / 36.0);
-}
-
 
 __global__ __launch_bounds__(256) void k_lbm(Lattice L, const double* __restrict__ src,
                                              double* __restrict__ dst) {
@@ -100,54 +72,26 @@ __global__ __launch_bounds__(256) void k_lbm_moments(Lattice L, const double* __
                                                      double* rho_o, double* u_o) {
   const long c = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= L.cells) return;
-  double rho = 0.0, mx = 0.0, my = 0.0, mz = 0.0;
-#pragma unroll
-  for (int i = 0; i < 19; ++i) {
-    const double v = f[i * L.cells + c];
-    rho += v;
-    mx += CX(i) * v; my += CY(i) * v; mz += CZ(i) * v;
-  }
+  double rho, ux, uy, uz;
+  cell_moments(L, f, c, rho, ux, uy, uz);
   rho_o[c] = rho;
-  u_o[c] = (mx + 0.5 * L.gx) / rho;
-  u_o[L.cells + c] = (my + 0.5 * L.gy) / rho;
-  u_o[2 * L.cells + c] = (mz + 0.5 * L.gz) / rho;
+  u_o[c] = ux;
+  u_o[L.cells + c] = uy;
+  u_o[2 * L.cells + c] = uz;
 }
 
 // ---------------------------------------------------------------- immersed boundary
-// Peskin's four-point delta along one axis.
-__device__ __forceinline__ double peskin4(double r) {
-  r = fabs(r);
-  if (r <= 1.0) return (3.0 - 2.0 * r + sqrt(1.0 + 4.0 * r - 4.0 * r * r)) * 0.125;
-  if (r <= 2.0) return (5.0 - 2.0 * r - sqrt(-7.0 + 12.0 * r - 4.0 * r * r)) * 0.125;
-  return 0.0;
-}
-
-// One node of the 4 x 4 x 4 stencil of position (x, y, z) per lane: lane k of
-// the particle's wave takes x offset k & 3, y offset (k >> 2) & 3, z offset
-// k >> 4 from floor - 1, so the 64 lanes of a wave touch 64 distinct nodes.
-// Returns the node's cell index (wrapped periodically) and its weight
-// (phi_z phi_y) phi_x. With walls in z a node beyond them takes no part: its
-// weight is 0 (and its index clamped into the lattice).
-__device__ __forceinline__ long stencil_node(const Lattice& L, double x, double y, double z, int k,
-                                             double& w) {
-  const int ox = k & 3, oy = (k >> 2) & 3, oz = k >> 4;
-  const int nx = (int)floor(x) - 1 + ox, ny = (int)floor(y) - 1 + oy, nz = (int)floor(z) - 1 + oz;
-  w = peskin4((double)nz - z) * peskin4((double)ny - y) * peskin4((double)nx - x);
-  const int ix = ((nx % L.nx) + L.nx) % L.nx, iy = ((ny % L.ny) + L.ny) % L.ny;
-  int iz;
-  if (L.walls) {
-    if (nz < 0 || nz >= L.nz) w = 0.0;
-    iz = nz < 0 ? 0 : (nz >= L.nz ? L.nz - 1 : nz);
-  } else {
-    iz = ((nz % L.nz) + L.nz) % L.nz;
-  }
-  return ((long)iz * L.ny + iy) * L.nx + ix;
-}
-
 // Fluid velocity at each particle: U(X) = sum over the 64 stencil nodes of
-// u(x) delta(x - X); u [3][cells] (the velocity plane of the moments). One
-// wave per particle, the node terms summed across the wave.
-__global__ __launch_bounds__(256) void k_ibm_interp(Lattice L, const double* __restrict__ u,
+// u(x) delta(x - X). One wave per particle, the node terms summed across the wave;
+// a lane forms its node's velocity from the 19 populations. The alternative, a pass that
+// first takes the velocity of every cell (u set), moves 184 B per cell, near a particle
+// or not, but forms a node's velocity once, where close particles share it. 10,314
+// particles, pass and read against direct: 73 and 30 us at 152 cells per particle, 31
+// and 29 at 64, 22 and 26 at 32, 19 and 21 at 16, 17 and 18 at 8 (and the pass is one
+// launch more).
+template <bool PASS>
+__global__ __launch_bounds__(256) void k_ibm_interp(Lattice L, const double* __restrict__ f,
+                                                   const double* __restrict__ u,
                                                    const double* __restrict__ X, long n,
                                                    double* U) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -156,7 +100,14 @@ __global__ __launch_bounds__(256) void k_ibm_interp(Lattice L, const double* __r
   const int k = (int)(t & 63);
   double w;
   const long c = stencil_node(L, X[p], X[n + p], X[2 * n + p], k, w);
-  double ax = u[c] * w, ay = u[L.cells + c] * w, az = u[2 * L.cells + c] * w;
+  double ux, uy, uz;
+  if constexpr (PASS) {
+    ux = u[c]; uy = u[L.cells + c]; uz = u[2 * L.cells + c];
+  } else {
+    double rho;
+    cell_moments(L, f, c, rho, ux, uy, uz);
+  }
+  double ax = ux * w, ay = uy * w, az = uz * w;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     ax += __shfl_xor(ax, o);
@@ -168,24 +119,10 @@ __global__ __launch_bounds__(256) void k_ibm_interp(Lattice L, const double* __r
   }
 }
 
-// Spread -scale F_p of every particle onto the force field g [3][cells]: one
-// wave per particle, each lane adding its node's share with a hardware FP64
-// atomic (device memory from hipMalloc is coarse-grained, where these are
-// exact adds; the sums agree to rounding with any order).
 __global__ __launch_bounds__(256) void k_ibm_spread(Lattice L, const double* __restrict__ X,
                                                    const double* __restrict__ F, long n,
                                                    double scale, double* g) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long p = t >> 6;
-  if (p >= n) return;
-  const int k = (int)(t & 63);
-  double w;
-  const long c = stencil_node(L, X[p], X[n + p], X[2 * n + p], k, w);
-  if (w == 0.0) return;  // outside the support, or beyond a wall
-  const double fx = -scale * F[p], fy = -scale * F[n + p], fz = -scale * F[2 * n + p];
-  unsafeAtomicAdd(&g[c], fx * w);
-  unsafeAtomicAdd(&g[L.cells + c], fy * w);
-  unsafeAtomicAdd(&g[2 * L.cells + c], fz * w);
+  ibm_spread(L, X, F, n, scale, g, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_fill0(double* a, long n) {
@@ -213,10 +150,19 @@ hipError_t launch_lbm_moments(const lbm_ctx* c, double* rho, double* u, hipStrea
                      (const double*)c->f[c->cur], rho, u);
   return hipGetLastError();
 }
-hipError_t launch_ibm_interp(const lbm_ctx* c, const double* u, const double* X, long n, double* U,
-                             hipStream_t s) {
+hipError_t launch_ibm_interp(const lbm_ctx* c, double* rho, double* u, const double* X, long n,
+                             double* U, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_ibm_interp, dim3(blocks_of(64 * n)), dim3(256), 0, s, c->L, u, X, n, U);
+  const double* f = c->f[c->cur];
+  if (32 * n <= c->L.cells) {  // (measured at k_ibm_interp)
+    hipLaunchKernelGGL(k_ibm_interp<false>, dim3(blocks_of(64 * n)), dim3(256), 0, s, c->L, f,
+                       (const double*)nullptr, X, n, U);
+    return hipGetLastError();
+  }
+  hipError_t e = launch_lbm_moments(c, rho, u, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_ibm_interp<true>, dim3(blocks_of(64 * n)), dim3(256), 0, s, c->L, f,
+                     (const double*)u, X, n, U);
   return hipGetLastError();
 }
 hipError_t launch_ibm_spread(const lbm_ctx* c, const double* X, const double* F, long n,

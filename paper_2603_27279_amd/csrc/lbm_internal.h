@@ -26,12 +26,13 @@ struct lbm_ctx {
 
 namespace lbmx {
 // One step with the uniform force plus gfield (nullable); the moments with the
-// uniform force's half shift; interpolation of u [3][cells] at X [3][n] into
-// U [3][n]; spreading of -scale F [3][n] at X into g [3][cells]; zero fill.
+// uniform force's half shift; the fluid velocity interpolated at X [3][n] into
+// U [3][n] (rho, u: scratch of [cells] and [3][cells] for the moments); spreading of
+// -scale F [3][n] at X into g [3][cells]; zero fill.
 hipError_t launch_lbm_step(lbm_ctx* c, const double* gfield, hipStream_t s);
 hipError_t launch_lbm_moments(const lbm_ctx* c, double* rho, double* u, hipStream_t s);
-hipError_t launch_ibm_interp(const lbm_ctx* c, const double* u, const double* X, long n, double* U,
-                             hipStream_t s);
+hipError_t launch_ibm_interp(const lbm_ctx* c, double* rho, double* u, const double* X, long n,
+                             double* U, hipStream_t s);
 hipError_t launch_ibm_spread(const lbm_ctx* c, const double* X, const double* F, long n,
                              double scale, double* g, hipStream_t s);
 hipError_t launch_fill0(double* a, long n, hipStream_t s);

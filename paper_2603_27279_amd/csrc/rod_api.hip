@@ -55,7 +55,7 @@ struct rod_ctx {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   Dev d;
   std::vector<void*> allocs;
-  double* ibm_buf = nullptr;  // coupled cycles: fluid velocity and penalty force [6][N]
+  double* ibm_buf = nullptr;  // coupled cycles: fluid velocity, penalty force, its positions [9][N]
   DipWork* work = nullptr;
   int nwork = 0, max_slots = 1;
   // with a dipole cutoff and a tape: all-pairs items of one slot for the
@@ -721,10 +721,14 @@ static int ewald_term(rod_ctx* c, const Dev& d) {
 }
 
 // build: rebuild the contact candidate lists of large systems this step.
-static int force_terms(rod_ctx* c, const Dev& d, int want_energy, int build) {
+// sp: spread the penalty force of the step before beside the forces (batched launches).
+static int force_terms(rod_ctx* c, const Dev& d, int want_energy, int build,
+                       const IbmSpread* sp = nullptr) {
   c->lists_stale = true;
   if (!want_energy && c->launch_mode == ROD_LAUNCH_BATCHED) {
-    TIMED(c, ROD_KERNEL_FORCES, launch_forces, d, c->desc.precision, c->work, c->nwork, c->s);
+    const hipEvent_t* ev = nullptr;
+    TRY(timing_events(c, ROD_KERNEL_FORCES, &ev));
+    HIPC(launch_forces(d, c->desc.precision, c->work, c->nwork, c->s, ev, sp));
     if (c->desc.contact_on && !contact_in_forces(d)) TRY(contact_term(c, d, 0, build));
     if (d.dcut > 0) TIMED(c, ROD_KERNEL_DIPOLE, launch_dipole_cut, d, build, c->s);
     if (d.ew_on) TRY(ewald_term(c, d));
@@ -1201,7 +1205,7 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
         (rc = dalloc(c, &d.dl_rec, (size_t)N)))
       return cleanup(rc);
   }
-  d.ibm_u = nullptr; d.ibm_f = nullptr; d.ibm_idt = 1.0;
+  d.ibm_u = nullptr; d.ibm_f = nullptr; d.ibm_x = nullptr; d.ibm_idt = 1.0;
   if (d.dcut > 0 && ((rc = dalloc(c, &d.dnbr, (size_t)DNBR_CAP * N)) ||
                      (rc = dalloc(c, &d.dnbr_cnt, (size_t)N)) ||
                      (rc = dalloc(c, &d.xm, 8 * (size_t)N))))
@@ -1819,10 +1823,11 @@ struct TmpDev {  // device memory of one call
 }  // namespace
 
 // Rods immersed in a lattice (Methods, "Immersed boundary coupling"). Per
-// cycle: moments of the lattice, its velocity interpolated at every particle,
-// then n_sub rod steps whose post kernel adds the penalty force and records it,
-// each followed by the spreading of -F_p / n_sub at the new positions, then one
-// lattice step with that force field. Everything runs on the rod stream; the
+// cycle: the lattice's velocity interpolated at every particle, then n_sub rod steps
+// whose gather adds the penalty force and records it, with the spreading of
+// -F_p / n_sub at each step's positions, then one lattice step with that force field.
+// Batched launches run the steps as the fused chain (pre, forces, (kick, forces)...,
+// post) and spread each step's force inside the next step's force launch. Everything runs on the rod stream; the
 // lattice stream is drained first and made to wait for the result.
 extern "C" int rod_lbm_cycles(rod_ctx* c, lbm_ctx* l, int32_t n_sub, int64_t n_cycles) {
   if (!c || !l) return fail(ROD_E_INVALID, "NULL argument");
@@ -1833,26 +1838,41 @@ extern "C" int rod_lbm_cycles(rod_ctx* c, lbm_ctx* l, int32_t n_sub, int64_t n_c
   if (n_cycles == 0) return ROD_OK;
   const long N = c->d.n, cells = l->L.cells;
   if (!l->work) HIPC(hipMalloc(&l->work, sizeof(double) * 7 * (size_t)cells));
-  if (!c->ibm_buf) HIPC(hipMalloc(&c->ibm_buf, sizeof(double) * 6 * (size_t)N));
+  if (!c->ibm_buf) HIPC(hipMalloc(&c->ibm_buf, sizeof(double) * 9 * (size_t)N));
   double* rho = l->work;
   double* u = rho + cells;
   double* g = u + 3 * cells;
   Dev d = c->d;
   d.ibm_u = c->ibm_buf;
   d.ibm_f = c->ibm_buf + 3 * N;
+  d.ibm_x = c->ibm_buf + 6 * N;
   d.ibm_idt = 1.0;
   HIPC(hipStreamSynchronize(l->s));
   TRY(enter(c));
   for (int64_t k = 0; k < n_cycles; ++k) {
-    HIPC(lbmx::launch_lbm_moments(l, rho, u, c->s));
-    HIPC(lbmx::launch_ibm_interp(l, u, d.x, N, c->ibm_buf, c->s));
+    HIPC(lbmx::launch_ibm_interp(l, rho, u, d.x, N, c->ibm_buf, c->s));
     HIPC(lbmx::launch_fill0(g, 3 * cells, c->s));
-    for (int32_t sub = 0; sub < n_sub; ++sub) {
+    if (c->launch_mode == ROD_LAUNCH_BATCHED) {
+      const IbmSpread sp{l->L, 1.0 / n_sub, g};
+      d.lc = 1;
       TIMED(c, ROD_KERNEL_PRE, launch_pre, d, PRE_STEP, c->s);
       TRY(force_terms(c, d, 0, 1));
+      for (int32_t sub = 1; sub < n_sub; ++sub) {
+        TIMED(c, ROD_KERNEL_KICK, launch_kick, d, nullptr, c->s);
+        d.lc = 3 - d.lc;
+        TRY(force_terms(c, d, 0, 0, &sp));
+      }
       TIMED(c, ROD_KERNEL_POST, launch_post, d, POST_KICK, ROD_TERM_ALL, nullptr, nullptr, nullptr,
             c->s);
       HIPC(lbmx::launch_ibm_spread(l, d.x, d.ibm_f, N, 1.0 / n_sub, g, c->s));
+    } else {
+      for (int32_t sub = 0; sub < n_sub; ++sub) {
+        TIMED(c, ROD_KERNEL_PRE, launch_pre, d, PRE_STEP, c->s);
+        TRY(force_terms(c, d, 0, 1));
+        TIMED(c, ROD_KERNEL_POST, launch_post, d, POST_KICK, ROD_TERM_ALL, nullptr, nullptr, nullptr,
+              c->s);
+        HIPC(lbmx::launch_ibm_spread(l, d.x, d.ibm_f, N, 1.0 / n_sub, g, c->s));
+      }
     }
     HIPC(lbmx::launch_lbm_step(l, g, c->s));
   }

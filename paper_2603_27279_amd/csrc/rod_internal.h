@@ -4,6 +4,8 @@
 #include <hip/hip_ext.h>
 #include <cstdint>
 
+#include "lbm_internal.h"
+
 namespace rodmx {
 
 // One entry of the hashed cell list: the particle's position at insertion and
@@ -186,7 +188,16 @@ struct Dev {
   // evaluation written to ibm_f [3][N], stiffness m_p * ibm_idt.
   const double* ibm_u;
   double* ibm_f;
+  double* ibm_x;           // [3][N] positions of that evaluation, put aside by the kick
   double ibm_idt;
+};
+
+// Spreading of a coupled cycle's penalty force, -scale ibm_f at ibm_x, onto the force
+// field g of lattice L inside the force launch.
+struct IbmSpread {
+  lbmx::Lattice L;
+  double scale;
+  double* g;
 };
 
 constexpr int BK_OWN = 255;                     // particles per block of the bond and kick pass
@@ -316,7 +327,8 @@ hipError_t launch_contact_lists(const Dev& d, hipStream_t s, const hipEvent_t* e
 // (candidate lists of large systems).
 inline bool contact_in_forces(const Dev& d) { return d.n < CONTACT_LANES_MAX_N; }
 hipError_t launch_forces(const Dev& d, int precision, const DipWork* work, int nwork,
-                         hipStream_t s, const hipEvent_t* ev = nullptr);
+                         hipStream_t s, const hipEvent_t* ev = nullptr,
+                         const IbmSpread* sp = nullptr);
 // The whole force pass of a level: launch_forces, and for systems whose contact
 // search is not part of it, launch_contact. build: rebuild the candidate lists.
 hipError_t launch_force_pass(const Dev& d, int precision, const DipWork* work, int nwork,
