@@ -316,7 +316,7 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E (vendor figure)
 #     boundary condition (10) in; x v q w (104) out
 BYTES = {"bond": 165.0, "bond_damped": 269.0, "contact": 52.0, "contact_hm": 128.0,
          "contact_hm_per_contact": 56.0, "dipole_cutoff": 100.0, "pre": 361.0,
-         "bond_kick": 330.0}
+         "bond_kick": 286.0}
 
 
 def hbm_microbench(sizes, steps=10):

@@ -5,8 +5,11 @@
 // and 506 B per particle; here the bond's results never leave the workgroup, and
 // what no later kernel of the chain reads is not written (the forces of a step that
 // is not the call's last, moments that only the all-pairs sum needs, cell-list
-// entries between rebuilds): 226 B in, 104 B out per particle (64 more with the
-// record of the dipole cutoff). 1.05M particles, mixed: 35 + 117 -> 75 us per step.
+// entries between rebuilds): 182 B in, 104 B out per particle (64 more with the
+// record of the dipole cutoff). Masses, inertias and the member come from a table by
+// rod, which neighbours share, and the bond's reference length from its vector: 44 B
+// less than from arrays by particle. 1.05M particles, mixed: 35 + 117 us per step as
+// two kernels, 75 fused, 67 with the table (4.5 TB/s).
 //
 // A bond needs both its particles at the level being closed, while the pass
 // overwrites them with the next level. Inside a workgroup they pass through LDS;
@@ -21,6 +24,13 @@
 #include "integrate_body.h"  // last: contraction within expressions from here on
 
 namespace rodmx {
+
+// The reference length of a bond as the host computes it for the other kernels:
+// products and sums rounded one by one.
+__device__ __forceinline__ double bond_length(V3<double> r) {
+#pragma clang fp contract(off)
+  return ::sqrt(r.x * r.x + r.y * r.y + r.z * r.z);
+}
 
 static_assert(BK_OWN == 255, "one thread of 256 evaluates the bond before the block");
 
@@ -56,13 +66,13 @@ __global__ __launch_bounds__(256) void k_bond_kick(Dev d, int last) {
   const uint8_t flags = any ? d.bflags[ii] : 0;
   const int rod = d.rod[ii];
   const V3<double> rref{d.bref[ii], d.bref[N + ii], d.bref[2 * N + ii]};
-  const double r0 = d.bref[3 * N + ii];
+  const double r0 = bond_length(rref);
   p.mb = ld3(d.mb, N, ii);
-  p.minv = d.minv[ii];
-  p.Iinv = d.Iinv[ii];
   p.b = d.bc[ii];
-  p.mem = d.mem[ii];
-  const double mass = d.mass[ii], inertia = d.inertia[ii];
+  p.minv = d.rodI[4 * (long)rod];
+  p.Iinv = d.rodI[4 * (long)rod + 1];
+  const double mass = d.rodI[4 * (long)rod + 2], inertia = d.rodI[4 * (long)rod + 3];
+  p.mem = d.rod_mem[rod];
   const V3<double> cF = d.contact_on ? ld3(d.cF, N, ii) : V3<double>{0.0, 0.0, 0.0};
   V3<double> cT{0.0, 0.0, 0.0}, Fd{0.0, 0.0, 0.0}, Bd{0.0, 0.0, 0.0};
   if constexpr (HM) cT = ld3(d.cT, N, ii);

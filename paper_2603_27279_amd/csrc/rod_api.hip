@@ -661,7 +661,7 @@ static size_t workspace_bytes(const rod_desc* d, int max_slots) {
   size_t N = d->n_particles, R = d->n_rods, M = d->n_members;
   size_t cells = d->contact_on ? next_pow2(std::max<size_t>(1024, 2 * N)) : 1;
   size_t b = 0;
-  b += N * (1 + 4 + 4 + 1) + 8 * N * 4 + 8 * N * 4 + 8 * R * 4 + 4 * M * 3 + 4 * (R + 1);  // topology
+  b += N * (1 + 4 + 4 + 1) + 8 * N * 4 + 8 * N * 4 + 8 * R * 8 + 4 * R + 4 * M * 3 + 4 * (R + 1);  // topology
   b += 8 * 3 * N + 4 * 3 * N + 8 * 9 * N + 8 * 4 * N;                         // mu, bonds
   b += 8 * (size_t)max_slots * 6 * N + 8 * 4 * N;                               // dipole, contact
   if (d->precision == ROD_MIXED && d->dipole_on) b += 4 * (size_t)max_slots * 6 * N;  // FP32 slots
@@ -1080,7 +1080,7 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   std::vector<uint8_t> bfl(N, 0);
   std::vector<int8_t> bc(dsc->bc, dsc->bc + N);
   std::vector<double> minv(N), Iinv(N), mass(N), inertia(N), bref(4 * (size_t)N, 0.0),
-      rodK(4 * (size_t)R);
+      rodK(4 * (size_t)R), rodI(4 * (size_t)R);
   std::vector<int> mrange(2 * M);
   for (int m = 0; m < M; ++m) { mrange[2 * m] = N; mrange[2 * m + 1] = 0; }
   const double pi = 3.14159265358979323846;
@@ -1095,6 +1095,8 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
     rodK[4 * r + 3] = E * I;         // K_b = EI / L
     const double pm = rho * pi * dd * dd * dd / 6.0;           // solid sphere
     const double pI = 0.4 * pm * (0.5 * dd) * (0.5 * dd);      // 2/5 m R^2
+    rodI[4 * r] = 1.0 / pm; rodI[4 * r + 1] = 1.0 / pI;
+    rodI[4 * r + 2] = pm; rodI[4 * r + 3] = pI;
     const int m = dsc->rod_member[r];
     for (int i = dsc->rod_offset[r]; i < dsc->rod_offset[r + 1]; ++i) {
       rod[i] = r; mem[i] = m;
@@ -1123,13 +1125,14 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   d.i_lo = 0; d.i_hi = N;
   d.x = b->x; d.v = b->v; d.q = b->q; d.w = b->w; d.F = b->force; d.T = b->torque;
   d.mb = b->m_body; d.field = b->field; d.extF = b->ext_force; d.extT = b->ext_torque;
-  uint8_t* bflags; int *rod_d, *rod_off_d, *mem_d, *mrange_d; int8_t* bc_d;
-  double *minv_d, *Iinv_d, *mass_d, *inertia_d, *bref_d, *rodK_d;
+  uint8_t* bflags; int *rod_d, *rod_off_d, *rod_mem_d, *mem_d, *mrange_d; int8_t* bc_d;
+  double *minv_d, *Iinv_d, *mass_d, *inertia_d, *bref_d, *rodK_d, *rodI_d;
   if ((rc = dalloc(c, &bflags, N)) || (rc = dalloc(c, &rod_d, N)) || (rc = dalloc(c, &mem_d, N)) ||
       (rc = dalloc(c, &rod_off_d, (size_t)R + 1)) ||
       (rc = dalloc(c, &bc_d, N)) || (rc = dalloc(c, &minv_d, N)) || (rc = dalloc(c, &Iinv_d, N)) ||
       (rc = dalloc(c, &mass_d, N)) || (rc = dalloc(c, &inertia_d, N)) ||
       (rc = dalloc(c, &bref_d, 4 * (size_t)N)) || (rc = dalloc(c, &rodK_d, 4 * (size_t)R)) ||
+      (rc = dalloc(c, &rodI_d, 4 * (size_t)R)) || (rc = dalloc(c, &rod_mem_d, (size_t)R)) ||
       (rc = dalloc(c, &mrange_d, 2 * (size_t)M)))
     return cleanup(rc);
   struct Up { void* dst; const void* src; size_t bytes; } ups[] = {
@@ -1139,6 +1142,7 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
       {minv_d, minv.data(), 8 * (size_t)N}, {Iinv_d, Iinv.data(), 8 * (size_t)N},
       {mass_d, mass.data(), 8 * (size_t)N}, {inertia_d, inertia.data(), 8 * (size_t)N},
       {bref_d, bref.data(), 32 * (size_t)N}, {rodK_d, rodK.data(), 32 * (size_t)R},
+      {rodI_d, rodI.data(), 32 * (size_t)R}, {rod_mem_d, c->rod_member_h.data(), 4 * (size_t)R},
       {mrange_d, mrange.data(), 8 * (size_t)M}};
   for (auto& u : ups)
     if (hipMemcpy(u.dst, u.src, u.bytes, hipMemcpyHostToDevice) != hipSuccess)
@@ -1146,6 +1150,7 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   d.bflags = bflags; d.rod = rod_d; d.rod_off = rod_off_d; d.mem = mem_d; d.bc = bc_d;
   d.minv = minv_d; d.Iinv = Iinv_d; d.mass = mass_d; d.inertia = inertia_d;
   d.bref = bref_d; d.rodK = rodK_d; d.mrange = mrange_d;
+  d.rodI = rodI_d; d.rod_mem = rod_mem_d;
   float* muf = nullptr;
   if ((rc = dalloc(c, &d.mu, 3 * (size_t)N)) || (rc = dalloc(c, &muf, 3 * (size_t)N)) ||
       (rc = dalloc(c, &d.bF, 3 * (size_t)N)) || (rc = dalloc(c, &d.bTs, 3 * (size_t)N)) ||

@@ -38,6 +38,8 @@ struct Dev {
   const double *minv, *Iinv, *mass, *inertia;
   const double* bref;      // [4N]: reference bond vector planes x, y, z and its length r0
   const double* rodK;      // [R][4]: EA, 12EI, GJ, EI
+  const double* rodI;      // [R][4]: 1 / mass, 1 / inertia, mass, inertia of its particles
+  const int* rod_mem;      // [R] member
   const int* mrange;       // [2M]: member particle range [begin, end)
   // per-step work buffers
   double* mu;              // [3N] global dipole moments
