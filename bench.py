@@ -311,9 +311,8 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E (vendor figure)
 #     (these systems) the cell-list entry (key, slot, count: 40 more) is written
 #     only at list rebuilds, by the contact launch
 #   bond and kick in one pass, as batched steps of these systems run (per
-#     particle): x v q w (104), m_body (24), reference vector and length (32),
-#     contact force (24), masses and inertias (32), rod and member ids, flags and
-#     boundary condition (10) in; x v q w (104) out
+#     particle): x v q w (104), m_body (24), reference vector (24), contact force
+#     (24), rod id, flags and boundary condition (6) in; x v q w (104) out
 BYTES = {"bond": 165.0, "bond_damped": 269.0, "contact": 52.0, "contact_hm": 128.0,
          "contact_hm_per_contact": 56.0, "dipole_cutoff": 100.0, "pre": 361.0,
          "bond_kick": 286.0}

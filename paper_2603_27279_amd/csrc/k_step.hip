@@ -182,8 +182,8 @@ __global__ __launch_bounds__(64 * (NW + 1)) void k_step(Dev d, StepOut o) {
   if (o.muf) st3(o.muf, N, i, V3<float>{(float)m.x, (float)m.y, (float)m.z});
 }
 
-// n steps of a member of at most STEPS_MAX particles from level lvl0, by one
-// workgroup: lane p < nm of the first wave owns particle p and evaluates its bond
+// n steps of a member of at most STEPS_MAX particles from the level in d.step[0], by
+// one workgroup: lane p < nm of the first wave owns particle p and evaluates its bond
 // while the other waves sum the dipoles, 64 / W targets at a time each. Everything
 // a particle has lives in LDS and is read where it is used: held in registers
 // across the loop, beside the bond's and the update's temporaries, it spilled
@@ -200,7 +200,7 @@ struct StepsSmem {
   int xr[STEPS_MAX][2];                    // index range of excluded neighbours
 };
 
-// With rec (a recorded run) level lvl0 + s goes to rec + s * rec_stride, in the
+// With rec (a recorded run from level lvl0) level lvl0 + s goes to rec + s * rec_stride, in the
 // planes of a recorded state followed by the dipole field, and the state read is
 // left as it was.
 template <class R, bool DAMP, int W>
@@ -214,6 +214,7 @@ __global__ __launch_bounds__(STEPS_THREADS) void k_steps(Dev d, long long lvl0, 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int NW = STEPS_THREADS / 64;
+  if (!rec) lvl0 = d.step[0];
   const bool own = tid < nm;
   const long i = b + (own ? tid : 0);
   const long l = own ? tid : 0;
@@ -321,7 +322,11 @@ __global__ __launch_bounds__(STEPS_THREADS) void k_steps(Dev d, long long lvl0, 
     }
     __syncthreads();
   }
-  if (b == 0 && tid == 0 && !rec) d.step[0] = lvl0 + n;
+  // the last workgroup to leave, when all have read the level
+  if (tid == 0 && !rec && atomicAdd(d.left, 1u) == gridDim.x - 1) {
+    *d.left = 0u;
+    d.step[0] = lvl0 + n;
+  }
 }
 
 template <class R, bool HM, bool DAMP>

@@ -767,18 +767,17 @@ static bool small_steps(const rod_ctx* c) {
   return c->launch_mode == ROD_LAUNCH_BATCHED && !c->timing && c->alt && !c->d.use_lists &&
          !c->d.ibm_u;
 }
-// Whether a launch serves many steps (a workgroup per member). Its level is an
-// argument, so it is never part of a captured graph.
+// Whether a launch serves many steps (a workgroup per member).
 static bool many_steps(const rod_ctx* c) {
   return small_steps(c) && !c->d.hm && c->max_member <= STEPS_MAX;
 }
 
-// n steps of a small system from level lvl, a launch per STEPS_LAUNCH of them (a
-// few milliseconds each).
+// n steps of a small system, a launch per STEPS_LAUNCH of them (a few milliseconds
+// each).
 constexpr int STEPS_LAUNCH = 1000;
-static int enqueue_many(rod_ctx* c, int64_t n, int64_t lvl) {
+static int enqueue_many(rod_ctx* c, int64_t n) {
   for (int64_t k = 0; k < n; k += STEPS_LAUNCH)
-    HIPC(launch_steps(c->d, c->desc.precision, c->max_member, lvl + k, (int)std::min<int64_t>(STEPS_LAUNCH, n - k),
+    HIPC(launch_steps(c->d, c->desc.precision, c->max_member, 0, (int)std::min<int64_t>(STEPS_LAUNCH, n - k),
                       c->s));
   return ROD_OK;
 }
@@ -827,10 +826,16 @@ static bool bond_kick_steps(const rod_ctx* c) {
 // pre kernel asks for new lists where a particle has moved too far since the last
 // build, whoever moved it, so lists outlive a call (open_bond_kick).
 static int open_bond_kick(rod_ctx* c) {  // before the chain, outside any captured graph
-  if (!bond_kick_steps(c) || !c->d.use_lists || !c->lists_stale) return ROD_OK;
+  if (!bond_kick_steps(c) || !c->d.use_lists) return ROD_OK;
+  // (a caller's capture runs at other times than this call: it rebuilds each time, and
+  // says nothing about the lists of the next call)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIPC(hipStreamIsCapturing(c->s, &cap));
+  const bool captured = cap != hipStreamCaptureStatusNone;
+  if (!captured && !c->lists_stale) return ROD_OK;
   // every position is far from a NaN: the chain's first step rebuilds
   HIPC(launch_fill_i32((int*)c->d.xb, 2, -1, c->s));
-  c->lists_stale = false;
+  c->lists_stale = captured;
   return ROD_OK;
 }
 static int enqueue_bond_kick(rod_ctx* c, int64_t n) {
@@ -1158,7 +1163,7 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
       (rc = dalloc(c, &d.cF, 3 * (size_t)N)) || (rc = dalloc(c, &d.cE, (size_t)N)) ||
       (rc = dalloc(c, &d.key, (size_t)N)) || (rc = dalloc(c, &d.ovf_list, 2 * (size_t)OVF_CAP)) ||
       (rc = dalloc(c, &d.ovf_cnt, 2)) || (rc = dalloc(c, &d.flags, FLAG_COUNT)) ||
-      (rc = dalloc(c, &d.step, 3)) ||
+      (rc = dalloc(c, &d.step, 3)) || (rc = dalloc(c, &d.left, 1)) ||
       (rc = dalloc(c, &c->epart, energy_doubles(N, M))) || (rc = dalloc(c, &c->eout, 9 * (size_t)M)) ||
       (rc = dalloc(c, &c->pair_count, 1)))
     return cleanup(rc);
@@ -1317,7 +1322,7 @@ int rod_step(rod_ctx* c, int64_t n) {
       TRY(tape_before_step(c->tape, c->d, c->s, c->h_step + k));
       if (many_steps(c)) {  // up to the next checkpoint, within the tape's capacity
         const int64_t m = std::min(std::min<int64_t>(every - rel % every, n - k), c->tape.capacity - rel);
-        TRY(enqueue_many(c, m, c->h_step + k));
+        TRY(enqueue_many(c, m));
         k += m;
       } else if (!c->timing && rel % every == 0 && n - k >= every && rel + every <= c->tape.capacity) {
         if (!c->tgexec) TRY(capture_steps(c, every, &c->tgexec));
@@ -1331,7 +1336,7 @@ int rod_step(rod_ctx* c, int64_t n) {
   } else if (c->launch_mode == ROD_LAUNCH_PER_ROD) {
     for (int64_t k = 0; k < n; ++k) TRY(enqueue_step_per_rod(c));
   } else if (many_steps(c)) {
-    TRY(enqueue_many(c, n, c->h_step));
+    TRY(enqueue_many(c, n));
   } else {
     int64_t left = n;
     if (!c->timing && c->desc.graph_steps > 0 && left >= c->desc.graph_steps) {

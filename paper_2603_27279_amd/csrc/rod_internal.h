@@ -81,6 +81,7 @@ struct Dev {
   // only in the copy its chain launches with.
   double* halo;
   double skin;             // list cutoff is r_c + skin
+  unsigned* left;          // workgroups of a many-step launch that have finished
   unsigned* flags;         // [FLAG_COUNT]: [0] non-finite state, [1] a dipole list was full,
                            // [2] overflow list full,
                            // [3] a particle had more Hertz-Mindlin contacts than HM_CAP,

@@ -18,9 +18,9 @@ struct StepOut {
 constexpr int STEPS_MAX = 32;  // particles of a member that k_steps can serve
 
 hipError_t launch_step(const Dev& d, int precision, const StepOut& o, hipStream_t s);
-// n steps from level lvl0 for every member, each of at most max_member <= STEPS_MAX
-// particles; not for Hertz-Mindlin contact. With rec every level is recorded there
-// and the state is left alone.
+// n steps from the level in d.step[0] for every member, each of at most max_member <=
+// STEPS_MAX particles; not for Hertz-Mindlin contact. With rec the levels after lvl0
+// are recorded there, and the state and its level are left alone.
 hipError_t launch_steps(const Dev& d, int precision, int max_member, long long lvl0, int n,
                         hipStream_t s, double* rec = nullptr, long rec_stride = 0);
 
