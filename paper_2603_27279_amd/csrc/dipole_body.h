@@ -18,6 +18,9 @@
 // accumulators. When a member's j range is split over several work items,
 // each writes its own FP64 partial slot, and the particle kernel adds the
 // slots in slot order (deterministic, no atomics, no cross-workgroup fences).
+// On the mixed path the slots are FP32 and their number belongs to the result; a
+// slot's tiles may still be taken by several work items (d.parts), whose FP64 partial
+// sums the particle kernel adds and rounds as the one item would have.
 #pragma once
 #include "rod_internal.h"
 #include "rod_math.h"
@@ -47,8 +50,6 @@ __device__ __forceinline__ float lane_value(float v) {
 
 __device__ __forceinline__ float minus5(float) { return lane_value(-5.0f); }
 __device__ __forceinline__ double minus5(double) { return -5.0; }
-
-constexpr int TJ = 512;   // j tile staged per workgroup (a quarter per wave)
 
 // Pair sums: f = sum s[(c - 5ab/r^2) r + a m_j], fm = sum s b,
 // bs = sum s b r, bm = sum m_j / r^3.
@@ -273,7 +274,10 @@ __device__ __forceinline__ void dipole_item(const Dev& d, const DipWork& wk, Dip
   if (wave == 0 && act) {
     for (int k = 0; k < NACC; ++k)
       F[k] = ((sm.red[0][k][lane] + sm.red[1][k][lane]) + sm.red[2][k][lane]) + sm.red[3][k][lane];
-    write_slot(slot_base<R>(d, wk.slot), N, i, d.C, F, mix, miy, miz);
+    if (sizeof(R) == 4 && d.parts > 1)
+      write_slot(d.dpart + (long)wk.slot * 6 * N, N, i, d.C, F, mix, miy, miz);
+    else
+      write_slot(slot_base<R>(d, wk.slot), N, i, d.C, F, mix, miy, miz);
   }
 }
 

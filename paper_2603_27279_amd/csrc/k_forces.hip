@@ -15,44 +15,51 @@ namespace rodmx {
 
 // HM: the lane-parallel search is the Hertz-Mindlin one (a kernel of its own,
 // k_forces_hm, so that the Hookean kernels keep their register budget).
-// FL (a coupled cycle): the last workgroups spread the penalty force of the step before
-// onto the lattice, from the positions and forces that the kick put aside. The spread
-// waits for its atomics and the dipole work items for their arithmetic, so it runs in
-// their shadow (10,314 particles: 25 us as a launch of its own, less than 1 us here).
+// FL (a coupled cycle): further workgroups spread the penalty force of the step before
+// onto the lattice, from the positions and forces that the kick put aside. They wait for
+// their atomics and the dipole work items for their arithmetic, so they are dispatched
+// among those: 10,314 particles, 25 us as a launch of its own; here 10 after a quarter
+// of the items, 11 after half, 13 behind all and 20 before them.
 template <class R, bool LANES, bool HM, bool FL>
 __device__ __forceinline__ void forces_body(const Dev& d, const DipWork* __restrict__ work,
-                                            int ndip, int nbond, int ncont, const IbmSpread& sp) {
+                                            int ndip, int nbond, const IbmSpread& sp) {
   __shared__ DipSmem<R> sm;
-  const int b = blockIdx.x;
+  int b = blockIdx.x;
+  if constexpr (FL) {
+    const int lead = ndip / 4, ns = (int)((d.n + 3) / 4);  // a wave per particle
+    if (b >= lead && b < lead + ns) {
+      lbmx::ibm_spread(sp.L, d.ibm_x, d.ibm_f, d.n, sp.scale, sp.g, b - lead);
+      return;
+    }
+    if (b >= lead) b -= ns;
+  }
   if (b < ndip) {
     if (d.dip_small) dipole_small_item<R>(d, work[b]);
     else dipole_item<R>(d, work[b], sm);
   } else if (b < ndip + nbond) {
     bond_thread<R>(d, d.i_lo + (long)(b - ndip) * 256 + threadIdx.x, 0);
-  } else if (!FL || b < ndip + nbond + ncont) {
-    if constexpr (LANES && HM) contact_hm_lanes<OUT_FORCE>(d, b - ndip - nbond);
-    else if constexpr (LANES) contact_pass<OUT_FORCE>(d, b - ndip - nbond, nullptr, 0, nullptr);
-  } else {
-    lbmx::ibm_spread(sp.L, d.ibm_x, d.ibm_f, d.n, sp.scale, sp.g, b - ndip - nbond - ncont);
+  } else if constexpr (LANES) {
+    if constexpr (HM) contact_hm_lanes<OUT_FORCE>(d, b - ndip - nbond);
+    else contact_pass<OUT_FORCE>(d, b - ndip - nbond, nullptr, 0, nullptr);
   }
 }
 
 template <class R, bool LANES>
 __global__ __launch_bounds__(256) void k_forces(Dev d, const DipWork* __restrict__ work, int ndip,
                                                 int nbond) {
-  forces_body<R, LANES, false, false>(d, work, ndip, nbond, 0, IbmSpread{});
+  forces_body<R, LANES, false, false>(d, work, ndip, nbond, IbmSpread{});
 }
 
 template <class R>
 __global__ __launch_bounds__(256) void k_forces_hm(Dev d, const DipWork* __restrict__ work,
                                                    int ndip, int nbond) {
-  forces_body<R, true, true, false>(d, work, ndip, nbond, 0, IbmSpread{});
+  forces_body<R, true, true, false>(d, work, ndip, nbond, IbmSpread{});
 }
 
 template <class R, bool LANES, bool HM>
 __global__ __launch_bounds__(256) void k_forces_fl(Dev d, const DipWork* __restrict__ work, int ndip,
-                                                   int nbond, int ncont, IbmSpread sp) {
-  forces_body<R, LANES, HM, true>(d, work, ndip, nbond, ncont, sp);
+                                                   int nbond, IbmSpread sp) {
+  forces_body<R, LANES, HM, true>(d, work, ndip, nbond, sp);
 }
 
 static void forces_kernel(const Dev& d, int precision, const DipWork* work, int ndip,
@@ -82,16 +89,15 @@ static void forces_kernel(const Dev& d, int precision, const DipWork* work, int 
   const dim3 g((unsigned)ndip + (unsigned)nbond + ncont), b(256);
   const bool hm = lanes && d.contact_on && d.hm;
   if (sp) {
-    const dim3 gs(g.x + (unsigned)((d.n + 3) / 4));  // a wave per particle
-    const int nc = (int)ncont;
+    const dim3 gs(g.x + (unsigned)((d.n + 3) / 4));
     if (precision == 1) {
-      if (hm) launch_k(ev, k_forces_fl<float, true, true>, gs, b, s, d, work, ndip, nbond, nc, *sp);
-      else if (lanes) launch_k(ev, k_forces_fl<float, true, false>, gs, b, s, d, work, ndip, nbond, nc, *sp);
-      else launch_k(ev, k_forces_fl<float, false, false>, gs, b, s, d, work, ndip, nbond, nc, *sp);
+      if (hm) launch_k(ev, k_forces_fl<float, true, true>, gs, b, s, d, work, ndip, nbond, *sp);
+      else if (lanes) launch_k(ev, k_forces_fl<float, true, false>, gs, b, s, d, work, ndip, nbond, *sp);
+      else launch_k(ev, k_forces_fl<float, false, false>, gs, b, s, d, work, ndip, nbond, *sp);
     } else {
-      if (hm) launch_k(ev, k_forces_fl<double, true, true>, gs, b, s, d, work, ndip, nbond, nc, *sp);
-      else if (lanes) launch_k(ev, k_forces_fl<double, true, false>, gs, b, s, d, work, ndip, nbond, nc, *sp);
-      else launch_k(ev, k_forces_fl<double, false, false>, gs, b, s, d, work, ndip, nbond, nc, *sp);
+      if (hm) launch_k(ev, k_forces_fl<double, true, true>, gs, b, s, d, work, ndip, nbond, *sp);
+      else if (lanes) launch_k(ev, k_forces_fl<double, true, false>, gs, b, s, d, work, ndip, nbond, *sp);
+      else launch_k(ev, k_forces_fl<double, false, false>, gs, b, s, d, work, ndip, nbond, *sp);
     }
     return;
   }

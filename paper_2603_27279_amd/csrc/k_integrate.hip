@@ -159,6 +159,26 @@ __device__ __forceinline__ void slot_sum(const T* dp, long N, int s_begin, int s
   }
 }
 
+// The same over slots in FP64 parts: a slot is the sum of its parts rounded to FP32, as
+// one work item would have stored it.
+__device__ __forceinline__ void slot_sum_parts(const double* dp, long N, int parts, int s_begin,
+                                               int s_end, long i, V3<double>& Fd, V3<double>& Bd) {
+  for (int s = s_begin; s < s_end; ++s) {
+    double v[PARTS_MAX][6];
+#pragma unroll
+    for (int k = 0; k < PARTS_MAX; ++k) {
+      const double* q = dp + ((long)s * parts + k) * 6 * N;
+#pragma unroll
+      for (int c = 0; c < 6; ++c) v[k][c] = k < parts ? q[c * N + i] : 0.0;
+    }
+    float f[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) f[c] = (float)(((v[0][c] + v[1][c]) + v[2][c]) + v[3][c]);
+    Fd = Fd + V3<double>{(double)f[0], (double)f[1], (double)f[2]};
+    Bd = Bd + V3<double>{(double)f[3], (double)f[4], (double)f[5]};
+  }
+}
+
 // The dipole force and field of particle i from slots [s_begin, s_end) when
 // `mask` asks for them (zero otherwise). Called first in the particle
 // kernels: the slot loads are the longest chain of the gather, and few other
@@ -168,7 +188,8 @@ __device__ __forceinline__ void dipole_sums(const Dev& d, long i, int mask, V3<d
   Fd = V3<double>{0.0, 0.0, 0.0};
   Bd = V3<double>{0.0, 0.0, 0.0};
   if (!((mask & 2) && d.dipole_on)) return;
-  if (d.dslotf) slot_sum<float, 8>(d.dslotf, d.n, s_begin, s_end, i, Fd, Bd);
+  if (d.parts > 1) slot_sum_parts(d.dpart, d.n, d.parts, s_begin, s_end, i, Fd, Bd);
+  else if (d.dslotf) slot_sum<float, 8>(d.dslotf, d.n, s_begin, s_end, i, Fd, Bd);
   else slot_sum<double, 8>(d.dpart, d.n, s_begin, s_end, i, Fd, Bd);
 }
 

@@ -373,6 +373,22 @@ static void spatial_order(const std::vector<double>& x, long N, int b, int e, in
 // DIP_SMALL_I targets against the whole member. small: -1 = automatic, 0 =
 // split, 1 = small, 2 = split in the spatial order of the current positions
 // (the ranges are then places in that order; see Dev::dperm).
+// Ranges of member m's sources in the split layout, f(j0, j1, slot): its slots, each cut
+// after the same number of whole tiles into c->d.parts parts.
+template <class F>
+static void dipole_ranges(const rod_ctx* c, int m, F&& f) {
+  const int b = c->mrange_h[2 * m], e = c->mrange_h[2 * m + 1];
+  const int len = c->mlen_h[m], parts = c->d.parts;
+  const int part = (((len + TJ - 1) / TJ + parts - 1) / parts) * TJ;
+  for (int s = 0; s < c->mslots_h[m]; ++s) {
+    const int j0 = b + s * len, j1 = std::min(e, j0 + len);
+    if (parts == 1) f(j0, j1, s);
+    else
+      for (int k = 0; k < parts && j0 + k * part < j1; ++k)
+        f(j0 + k * part, std::min(j1, j0 + (k + 1) * part), s * parts + k);
+  }
+}
+
 static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
   const std::vector<int>& mrange = c->mrange_h;
   const int M = c->desc.n_members;
@@ -391,8 +407,13 @@ static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
   for (void* p : c->plan_allocs) (void)hipFree(p);
   c->plan_allocs.clear();
   std::vector<DipWork> items;
-  std::vector<int> mslots(M, 1), mlen(M, 0);
+  c->mslots_h.assign(M, 1);
+  c->mlen_h.assign(M, 0);
+  c->d.parts = 1;
+  std::vector<int>&mslots = c->mslots_h, &mlen = c->mlen_h;
   int max_slots = 1;
+  long nitems = 0, tiles = 0;  // split layout: items of whole slots, tiles of the longest
+  const bool split = !small && c->d.dcut == 0.0 && !c->d.ew_on;
   // with a dipole cutoff the list walk writes slot 0, and with a periodic box the
   // Ewald sum does: there are no work items
   for (int m = 0; m < M && c->d.dcut == 0.0 && !c->d.ew_on; ++m) {
@@ -413,15 +434,28 @@ static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
     mslots[m] = S;
     mlen[m] = len;
     max_slots = std::max(max_slots, S);
-    for (int i0 = b; i0 < e; i0 += 64)
-      for (int s = 0; s < S; ++s) {
-        DipWork w{};
-        w.i0 = i0; w.i1 = std::min(i0 + 64, e);
-        w.j0 = b + s * len; w.j1 = std::min(e, b + (s + 1) * len);
-        w.slot = s;
-        items.push_back(w);
-      }
+    nitems += (long)((nm + 63) / 64) * S;
+    tiles = std::max<long>(tiles, (len + TJ - 1) / TJ);
   }
+  // Parts of a slot on the mixed path: towards 4096 items. With some 1024, four per
+  // compute unit, the last ones leave units idle. Slots whole and in parts, us per step
+  // of separate rods of 64: 4,608 particles 40.4 and 39.8, 8,192 74.8 and 71.7, 10,304
+  // 122 and 107, 16,384 254 and 230, 32,768 948 and 849, 65,536 3,722 and 3,231. (FP64
+  // has more slots instead, default_work_items.)
+  if (split && c->desc.precision == ROD_MIXED && c->desc.dipole_on && nitems > 0)
+    c->d.parts = (int)std::max<long>(1, std::min<long>(std::min<long>(tiles, PARTS_MAX), 4096 / nitems));
+  // The last part of a slot may be shorter: all first parts, then all second ones, or the
+  // round of workgroups over the dies would give some dies nothing but short items.
+  for (int k = 0; k < c->d.parts; ++k)
+    for (int m = 0; m < M && split; ++m)
+      for (int i0 = mrange[2 * m]; i0 < mrange[2 * m + 1]; i0 += 64)
+        dipole_ranges(c, m, [&](int j0, int j1, int slot) {
+          if (slot % c->d.parts != k) return;
+          DipWork w{};
+          w.i0 = i0; w.i1 = std::min(i0 + 64, mrange[2 * m + 1]);
+          w.j0 = j0; w.j1 = j1; w.slot = slot;
+          items.push_back(w);
+        });
   // the reverse pass of a dipole cutoff: every pair of a member in one slot,
   // each tested against the cutoff (the forward walks its lists instead)
   std::vector<DipWork> adj;
@@ -440,8 +474,6 @@ static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
     TRY(palloc(c, &c->adj_work, adj.size()));
     HIPC(hipMemcpy(c->adj_work, adj.data(), adj.size() * sizeof(DipWork), hipMemcpyHostToDevice));
   }
-  c->mslots_h = mslots;
-  c->mlen_h = mlen;
   c->d.dip_small = small ? 1 : 0;
   c->max_member = max_member;
   c->alt = nullptr;
@@ -475,11 +507,13 @@ static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
     HIPC(hipMemcpy(c->work, items.data(), items.size() * sizeof(DipWork), hipMemcpyHostToDevice));
   int* ms = nullptr;
   TRY(palloc(c, &ms, M));
-  HIPC(hipMemcpy(ms, mslots.data(), M * sizeof(int), hipMemcpyHostToDevice));
+  std::vector<int> planes(mslots);
+  for (int& s : planes) s *= c->d.parts;
+  HIPC(hipMemcpy(ms, planes.data(), M * sizeof(int), hipMemcpyHostToDevice));
   c->d.mslots = ms;
-  TRY(palloc(c, &c->d.dpart, (size_t)max_slots * 6 * N));
+  TRY(palloc(c, &c->d.dpart, (size_t)max_slots * c->d.parts * 6 * N));
   c->d.dslotf = nullptr;
-  if (c->desc.precision == ROD_MIXED && c->desc.dipole_on && c->d.dcut == 0.0 && !c->d.ew_on)
+  if (c->d.parts == 1 && c->desc.precision == ROD_MIXED && c->desc.dipole_on && c->d.dcut == 0.0 && !c->d.ew_on)
     TRY(palloc(c, &c->d.dslotf, (size_t)max_slots * 6 * N));
   return ROD_OK;
 }
@@ -922,13 +956,11 @@ static int build_rod_work(rod_ctx* c) {
         w.i0 = i0; w.i1 = i1; w.j0 = b; w.j1 = e; w.slot = 0;
         items.push_back(w);
       } else {
-        for (int s = 0; s < c->mslots_h[m]; ++s) {
+        dipole_ranges(c, m, [&](int j0, int j1, int slot) {
           DipWork w{};
-          w.i0 = i0; w.i1 = i1;
-          w.j0 = b + s * c->mlen_h[m]; w.j1 = std::min(e, b + (s + 1) * c->mlen_h[m]);
-          w.slot = s;
+          w.i0 = i0; w.i1 = i1; w.j0 = j0; w.j1 = j1; w.slot = slot;
           items.push_back(w);
-        }
+        });
       }
     }
     c->rod_work_off.push_back((int)items.size());
@@ -1049,7 +1081,8 @@ const char* rod_last_error(void) { return g_err.c_str(); }
 int rod_query_workspace(const rod_desc* d, size_t* bytes) {
   TRY(validate(d));
   if (!bytes) return fail(ROD_E_INVALID, "bytes is NULL");
-  *bytes = workspace_bytes(d, default_work_items(d) > 1024 ? 32 : 16);
+  // (from 8,192 particles more slots, or FP64 parts of slots; one each from 65,536 on)
+  *bytes = workspace_bytes(d, d->n_particles >= 8192 && (d->precision == ROD_FP64 || d->n_particles < 65536) ? 32 : 16);
   return ROD_OK;
 }
 
@@ -1615,7 +1648,7 @@ int rod_grad(rod_ctx* c, const rod_cotangent* gy, rod_gradients* gx) {
     small.many = many_steps(c) ? c->max_member : 0;
   }
   TRY(adjoint_run(c->tape, c->d, c->desc.precision, cut ? c->adj_work : c->work,
-                  cut ? c->adj_nwork : c->nwork, c->max_slots, small, c->s, c->h_step, gy, gx));
+                  cut ? c->adj_nwork : c->nwork, c->max_slots * c->d.parts, small, c->s, c->h_step, gy, gx));
   TRY(leave(c));
   return ROD_OK;
 }

@@ -52,6 +52,8 @@ struct Dev {
   const double* bdamp;     // [R][4] bond damping factors g_r, g_s, g_t, g_b, or null (none)
   double* hist;            // [2][5][N] bond damping measures per level parity (bond k at k)
   const int* mslots;       // [M]: j ranges (partial slots) of each member
+  int parts;               // work items per slot: above 1 (mixed path, split layout) each
+                           // writes an FP64 part of the slot to dpart, [S][parts][6][N]
   int max_slots;           // largest entry of mslots; slots a member does not use stay zero
   double* cF;              // [3N] contact force
   double* cE;              // [N] contact energy per particle (energy evaluation only)
@@ -251,8 +253,10 @@ enum PostMode { POST_PREPARE = 0, POST_KICK = 1, POST_EVAL = 2 };
 
 // One dipole work item: an i block [i0, i1) of at most 64 particles of one
 // member against j in [j0, j1) of the same member,
-// written to partial slot `slot`.
+// written to partial slot `slot` (slot s of d.parts parts: s parts + the part).
 struct DipWork { int i0, i1, j0, j1, slot, pad0, pad1, pad2; };
+constexpr int TJ = 512;  // j tile staged per workgroup of the split layout (a quarter per wave)
+constexpr int PARTS_MAX = 4;
 
 
 // Targets per work item of the small-member layout (one wave of a 256-thread
