@@ -218,8 +218,11 @@ union DipSmem {
 };
 
 // One work item of the split layout (256 threads). Its ranges are positions:
-// particles themselves, or places in the spatial order (d.dperm).
-template <class R>
+// particles themselves, or places in the spatial order (d.dperm). PARTS: whether it
+// writes part of a slot (a template argument where the kernel is bound by this code:
+// the test and the second form of the store cost the whole slots 0.5%).
+enum DipParts { WHOLE_SLOTS, SLOT_PARTS, BY_PLAN };
+template <class R, DipParts PARTS = BY_PLAN>
 __device__ __forceinline__ void dipole_item(const Dev& d, const DipWork& wk, DipSmem<R>& sm) {
   Src<R>* tile = sm.st.tile;
   const long N = d.n;
@@ -274,7 +277,7 @@ __device__ __forceinline__ void dipole_item(const Dev& d, const DipWork& wk, Dip
   if (wave == 0 && act) {
     for (int k = 0; k < NACC; ++k)
       F[k] = ((sm.red[0][k][lane] + sm.red[1][k][lane]) + sm.red[2][k][lane]) + sm.red[3][k][lane];
-    if (sizeof(R) == 4 && d.parts > 1)
+    if (sizeof(R) == 4 && (PARTS == SLOT_PARTS || (PARTS == BY_PLAN && d.parts > 1)))
       write_slot(d.dpart + (long)wk.slot * 6 * N, N, i, d.C, F, mix, miy, miz);
     else
       write_slot(slot_base<R>(d, wk.slot), N, i, d.C, F, mix, miy, miz);

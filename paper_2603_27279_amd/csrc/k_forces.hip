@@ -20,7 +20,7 @@ namespace rodmx {
 // their atomics and the dipole work items for their arithmetic, so they are dispatched
 // among those: 10,314 particles, 25 us as a launch of its own; here 10 after a quarter
 // of the items, 11 after half, 13 behind all and 20 before them.
-template <class R, bool LANES, bool HM, bool FL>
+template <class R, bool LANES, bool HM, bool FL, DipParts PARTS = BY_PLAN>
 __device__ __forceinline__ void forces_body(const Dev& d, const DipWork* __restrict__ work,
                                             int ndip, int nbond, const IbmSpread& sp) {
   __shared__ DipSmem<R> sm;
@@ -35,7 +35,7 @@ __device__ __forceinline__ void forces_body(const Dev& d, const DipWork* __restr
   }
   if (b < ndip) {
     if (d.dip_small) dipole_small_item<R>(d, work[b]);
-    else dipole_item<R>(d, work[b], sm);
+    else dipole_item<R, PARTS>(d, work[b], sm);
   } else if (b < ndip + nbond) {
     bond_thread<R>(d, d.i_lo + (long)(b - ndip) * 256 + threadIdx.x, 0);
   } else if constexpr (LANES) {
@@ -44,10 +44,10 @@ __device__ __forceinline__ void forces_body(const Dev& d, const DipWork* __restr
   }
 }
 
-template <class R, bool LANES>
+template <class R, bool LANES, DipParts PARTS = WHOLE_SLOTS>
 __global__ __launch_bounds__(256) void k_forces(Dev d, const DipWork* __restrict__ work, int ndip,
                                                 int nbond) {
-  forces_body<R, LANES, false, false>(d, work, ndip, nbond, IbmSpread{});
+  forces_body<R, LANES, false, false, PARTS>(d, work, ndip, nbond, IbmSpread{});
 }
 
 template <class R>
@@ -103,6 +103,8 @@ static void forces_kernel(const Dev& d, int precision, const DipWork* work, int 
   }
   if (precision == 1) {
     if (hm) launch_k(ev, k_forces_hm<float>, g, b, s, d, work, ndip, nbond);
+    else if (lanes && d.parts > 1) launch_k(ev, k_forces<float, true, SLOT_PARTS>, g, b, s, d, work, ndip, nbond);
+    else if (d.parts > 1) launch_k(ev, k_forces<float, false, SLOT_PARTS>, g, b, s, d, work, ndip, nbond);
     else if (lanes) launch_k(ev, k_forces<float, true>, g, b, s, d, work, ndip, nbond);
     else launch_k(ev, k_forces<float, false>, g, b, s, d, work, ndip, nbond);
   } else {
