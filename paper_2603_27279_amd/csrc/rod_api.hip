@@ -479,8 +479,8 @@ static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
   c->alt = nullptr;
   c->alt_muf = nullptr;
   if (small && c->d.dcut == 0.0 && !c->d.ew_on) {
-    TRY(palloc(c, &c->alt, 16 * (size_t)N));
-    if (c->d.muf) TRY(palloc(c, &c->alt_muf, 3 * (size_t)N));
+    TRY(palloc(c, &c->alt, (c->d.muf ? 18 : 16) * (size_t)N));  // and the FP32 moments
+    if (c->d.muf) c->alt_muf = (float*)(c->alt + 16 * (size_t)N);
   }
   c->plan_small = spatial ? 2 : small ? 1 : 0;
   c->d.dperm = nullptr;
@@ -1156,6 +1156,13 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   c->bflags_h = bfl;
   c->rod_h = rod;
 
+  // per-rod tables in one block: rodK, rodI, rod_off [R + 1] and rod_mem [R]
+  std::vector<double> rod_table(8 * (size_t)R + R + 1);
+  std::copy(rodK.begin(), rodK.end(), rod_table.begin());
+  std::copy(rodI.begin(), rodI.end(), rod_table.begin() + 4 * (size_t)R);
+  std::memcpy(&rod_table[8 * (size_t)R], c->rod_offset.data(), 4 * ((size_t)R + 1));
+  std::memcpy((int*)&rod_table[8 * (size_t)R] + R + 1, c->rod_member_h.data(), 4 * (size_t)R);
+
   // ---- device workspace
   Dev& d = c->d;
   d = Dev{};
@@ -1163,32 +1170,29 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   d.i_lo = 0; d.i_hi = N;
   d.x = b->x; d.v = b->v; d.q = b->q; d.w = b->w; d.F = b->force; d.T = b->torque;
   d.mb = b->m_body; d.field = b->field; d.extF = b->ext_force; d.extT = b->ext_torque;
-  uint8_t* bflags; int *rod_d, *rod_off_d, *rod_mem_d, *mem_d, *mrange_d; int8_t* bc_d;
-  double *minv_d, *Iinv_d, *mass_d, *inertia_d, *bref_d, *rodK_d, *rodI_d;
+  uint8_t* bflags; int *rod_d, *mem_d, *mrange_d; int8_t* bc_d;
+  double *minv_d, *Iinv_d, *mass_d, *inertia_d, *bref_d, *rodK_d;
   if ((rc = dalloc(c, &bflags, N)) || (rc = dalloc(c, &rod_d, N)) || (rc = dalloc(c, &mem_d, N)) ||
-      (rc = dalloc(c, &rod_off_d, (size_t)R + 1)) ||
       (rc = dalloc(c, &bc_d, N)) || (rc = dalloc(c, &minv_d, N)) || (rc = dalloc(c, &Iinv_d, N)) ||
       (rc = dalloc(c, &mass_d, N)) || (rc = dalloc(c, &inertia_d, N)) ||
-      (rc = dalloc(c, &bref_d, 4 * (size_t)N)) || (rc = dalloc(c, &rodK_d, 4 * (size_t)R)) ||
-      (rc = dalloc(c, &rodI_d, 4 * (size_t)R)) || (rc = dalloc(c, &rod_mem_d, (size_t)R)) ||
+      (rc = dalloc(c, &bref_d, 4 * (size_t)N)) || (rc = dalloc(c, &rodK_d, rod_table.size())) ||
       (rc = dalloc(c, &mrange_d, 2 * (size_t)M)))
     return cleanup(rc);
   struct Up { void* dst; const void* src; size_t bytes; } ups[] = {
-      {rod_off_d, c->rod_offset.data(), 4 * ((size_t)R + 1)},
       {bflags, bfl.data(), (size_t)N}, {rod_d, rod.data(), 4 * (size_t)N},
       {mem_d, mem.data(), 4 * (size_t)N}, {bc_d, bc.data(), (size_t)N},
       {minv_d, minv.data(), 8 * (size_t)N}, {Iinv_d, Iinv.data(), 8 * (size_t)N},
       {mass_d, mass.data(), 8 * (size_t)N}, {inertia_d, inertia.data(), 8 * (size_t)N},
-      {bref_d, bref.data(), 32 * (size_t)N}, {rodK_d, rodK.data(), 32 * (size_t)R},
-      {rodI_d, rodI.data(), 32 * (size_t)R}, {rod_mem_d, c->rod_member_h.data(), 4 * (size_t)R},
+      {bref_d, bref.data(), 32 * (size_t)N}, {rodK_d, rod_table.data(), 8 * rod_table.size()},
       {mrange_d, mrange.data(), 8 * (size_t)M}};
   for (auto& u : ups)
     if (hipMemcpy(u.dst, u.src, u.bytes, hipMemcpyHostToDevice) != hipSuccess)
       return cleanup(fail(ROD_E_HIP, "upload failed"));
-  d.bflags = bflags; d.rod = rod_d; d.rod_off = rod_off_d; d.mem = mem_d; d.bc = bc_d;
+  d.bflags = bflags; d.rod = rod_d; d.mem = mem_d; d.bc = bc_d;
   d.minv = minv_d; d.Iinv = Iinv_d; d.mass = mass_d; d.inertia = inertia_d;
   d.bref = bref_d; d.rodK = rodK_d; d.mrange = mrange_d;
-  d.rodI = rodI_d; d.rod_mem = rod_mem_d;
+  d.rodI = rodK_d + 4 * (size_t)R;
+  d.rod_off = (const int*)(rodK_d + 8 * (size_t)R); d.rod_mem = d.rod_off + R + 1;
   float* muf = nullptr;
   if ((rc = dalloc(c, &d.mu, 3 * (size_t)N)) || (rc = dalloc(c, &muf, 3 * (size_t)N)) ||
       (rc = dalloc(c, &d.bF, 3 * (size_t)N)) || (rc = dalloc(c, &d.bTs, 3 * (size_t)N)) ||
@@ -1196,10 +1200,11 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
       (rc = dalloc(c, &d.cF, 3 * (size_t)N)) || (rc = dalloc(c, &d.cE, (size_t)N)) ||
       (rc = dalloc(c, &d.key, (size_t)N)) || (rc = dalloc(c, &d.ovf_list, 2 * (size_t)OVF_CAP)) ||
       (rc = dalloc(c, &d.ovf_cnt, 2)) || (rc = dalloc(c, &d.flags, FLAG_COUNT)) ||
-      (rc = dalloc(c, &d.step, 3)) || (rc = dalloc(c, &d.left, 1)) ||
+      (rc = dalloc(c, &d.step, 4)) ||
       (rc = dalloc(c, &c->epart, energy_doubles(N, M))) || (rc = dalloc(c, &c->eout, 9 * (size_t)M)) ||
       (rc = dalloc(c, &c->pair_count, 1)))
     return cleanup(rc);
+  d.left = (unsigned*)(d.step + 3);
   d.muf = dsc->precision == ROD_MIXED ? muf : nullptr;
   if (dsc->precision == ROD_MIXED && dsc->dipole_on) {
     if ((rc = dalloc(c, &d.cbox, 6 * (size_t)((N + 63) / 64)))) return cleanup(rc);
