@@ -233,6 +233,7 @@ __device__ __forceinline__ void contact_listed(const Dev& d, long blk, bool buil
       d.nbr_cnt[i] = nc <= NBR_CAP ? nc : -1;
       if (nc > NBR_CAP) atomicOr(&d.rebuild[2], 1u);
       st3(d.xb, N, i, xi);
+      if (i == 0) d.rebuild[3] = 1u;  // (k_bond_kick takes it back)
     } else {
       for_cell_candidates(d, tab, xi, mem, [&](int j, int rj, V3<double> xj) {
         if (!excluded(j, rj)) force(xj);
@@ -378,6 +379,7 @@ __device__ __forceinline__ void contact_hm_thread(const Dev& d, long blk, bool b
       d.nbr_cnt[i] = nc <= NBR_CAP ? nc : -1;
       if (nc > NBR_CAP) atomicOr(&d.rebuild[2], 1u);
       st3(d.xb, N, i, xi);
+      if (i == 0) d.rebuild[3] = 1u;  // (k_bond_kick takes it back)
     }
   }
   if (d.hist_write) {

@@ -209,6 +209,7 @@ __device__ __forceinline__ void dipole_list_build(const Dev& d, unsigned blk, un
     d.dnbr_cnt[t] = min(nc, DNBR_CAP);
     if (nc > DNBR_CAP) atomicOr(&d.flags[FLAG_DIP_OVF], 1u);
     st3(d.xb, N, i, xi);
+    if (i == 0) d.rebuild[3] = 1u;  // (k_bond_kick takes it back)
   }
 }
 

@@ -125,6 +125,7 @@ __global__ __launch_bounds__(256) void k_bond_kick(Dev d, int last) {
     else d.step[3 - d.lc] = L + 1;
     if (d.use_lists) {  // (the launches that read these are over)
       d.rebuild[d.lc & 1] = 0u;
+      d.rebuild[3] = 0u;  // (and every list is the chain's)
       d.cell_dirty[(d.lc & 1) ^ 1] = 0;
     }
   }

@@ -69,9 +69,6 @@ struct rod_ctx {
   // of the fused steps of small systems, or null.
   double* alt = nullptr;
   double* halo = nullptr;  // Dev::halo of the fused bond and kick pass, or null
-  // Something other than that pass's chain may have rebuilt one of the candidate
-  // lists (or none is built yet): the chain's next call rebuilds them all.
-  bool lists_stale = true;
   float* alt_muf = nullptr;
   int plan_small = -1, plan_target = 1024;  // current dipole layout
   std::vector<int> mslots_h;        // [M] source ranges per member of the current layout
@@ -758,7 +755,6 @@ static int ewald_term(rod_ctx* c, const Dev& d) {
 // sp: spread the penalty force of the step before beside the forces (batched launches).
 static int force_terms(rod_ctx* c, const Dev& d, int want_energy, int build,
                        const IbmSpread* sp = nullptr) {
-  c->lists_stale = true;
   if (!want_energy && c->launch_mode == ROD_LAUNCH_BATCHED) {
     const hipEvent_t* ev = nullptr;
     TRY(timing_events(c, ROD_KERNEL_FORCES, &ev));
@@ -858,18 +854,17 @@ static bool bond_kick_steps(const rod_ctx* c) {
 
 // n steps: pre, then contact (and the cutoff walk) and the fused pass per step. The
 // pre kernel asks for new lists where a particle has moved too far since the last
-// build, whoever moved it, so lists outlive a call (open_bond_kick).
+// build, whoever moved it, or where something else has built a list since the chain's
+// own last build (Dev::rebuild[3], a device word, so that evaluations which the caller
+// captured and replays are seen too): lists outlive a call.
+// A call that the caller captures rebuilds in every replay (the dipole sums of a cutoff
+// run in list order: replays then give the bits of eager calls after an inspection).
 static int open_bond_kick(rod_ctx* c) {  // before the chain, outside any captured graph
   if (!bond_kick_steps(c) || !c->d.use_lists) return ROD_OK;
-  // (a caller's capture runs at other times than this call: it rebuilds each time, and
-  // says nothing about the lists of the next call)
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   HIPC(hipStreamIsCapturing(c->s, &cap));
-  const bool captured = cap != hipStreamCaptureStatusNone;
-  if (!captured && !c->lists_stale) return ROD_OK;
-  // every position is far from a NaN: the chain's first step rebuilds
-  HIPC(launch_fill_i32((int*)c->d.xb, 2, -1, c->s));
-  c->lists_stale = captured;
+  if (cap != hipStreamCaptureStatusNone)
+    HIPC(launch_fill_i32((int*)c->d.rebuild + 3, 1, 1, c->s));
   return ROD_OK;
 }
 static int enqueue_bond_kick(rod_ctx* c, int64_t n) {
@@ -975,7 +970,6 @@ static int build_rod_work(rod_ctx* c) {
 
 // The plain per-rod loop: every kernel launched once per rod on that rod's particles.
 static int enqueue_step_per_rod(rod_ctx* c) {
-  c->lists_stale = true;
   const int R = c->desc.n_rods;
   auto rod_dev = [&](int r) {
     Dev dr = c->d;
@@ -1263,9 +1257,12 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
   if ((rc = ewald_setup(c, dsc, mrange))) return cleanup(rc);
   if (d.use_lists &&
       ((rc = dalloc(c, &d.nbr, (size_t)NBR_CAP * N)) || (rc = dalloc(c, &d.nbr_cnt, (size_t)N)) ||
-       (rc = dalloc(c, &d.xb, 3 * (size_t)N)) || (rc = dalloc(c, &d.rebuild, 3)) ||
+       (rc = dalloc(c, &d.xb, 3 * (size_t)N)) || (rc = dalloc(c, &d.rebuild, 4)) ||
        (rc = dalloc(c, &d.cell_dirty, 2))))
     return cleanup(rc);
+  const unsigned rebuild0[4] = {0u, 0u, 0u, 1u};
+  if (d.use_lists && hipMemcpy(d.rebuild, rebuild0, sizeof(rebuild0), hipMemcpyHostToDevice) != hipSuccess)
+    return cleanup(fail(ROD_E_HIP, "upload failed"));
   if (((long)N >= CONTACT_LANES_MAX_N || d.dcut > 0) && !d.ew_on && (!dsc->dipole_on || d.dcut > 0) &&
       (rc = dalloc(c, &c->halo, 40 * (size_t)((N + BK_OWN - 1) / BK_OWN))))
     return cleanup(rc);
@@ -1645,7 +1642,6 @@ int rod_grad(rod_ctx* c, const rod_cotangent* gy, rod_gradients* gx) {
     return fail(ROD_E_NOTAPE, "no recorded steps: call rod_tape_begin, then rod_step");
   TRY(enter(c));
   const bool cut = c->d.dcut > 0.0;
-  c->lists_stale = true;
   TapeSmall small;
   if (small_steps(c)) {
     small.mu = c->alt + 13 * c->d.n;

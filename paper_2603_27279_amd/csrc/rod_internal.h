@@ -76,7 +76,10 @@ struct Dev {
   double* xb;              // [3N] positions at the last build
   unsigned* rebuild;       // [2] by the parity of lc: some particle moved too far since the build;
                            // [2] a list of the last build had more than NBR_CAP candidates (its
-                           // particle searches the cells, which are then filled every step)
+                           // particle searches the cells, which are then filled every step);
+                           // [3] a list was built, or the positions of the last build were set,
+                           // by something else than the chain of the fused bond and kick pass
+                           // (or nothing is built yet): the chain's next call rebuilds all lists
   int* cell_dirty;         // [2] by the parity of lc: k_cell_insert filled that evaluation's table
   // Fused bond and kick pass of large systems (k_bond_kick.hip): the first and last
   // particle (x, q, v) of each block of BK_OWN, [2 level parities][blocks][2][10]; set
