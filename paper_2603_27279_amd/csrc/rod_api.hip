@@ -1398,6 +1398,11 @@ int rod_sync(rod_ctx* c) {
   if (any) {
     unsigned z[FLAG_COUNT] = {};
     HIPC(hipMemcpy(c->d.flags, z, sizeof(z), hipMemcpyHostToDevice));
+    // a truncated list or cell table is not walked by a later call as if it were whole:
+    // the lists are built anew there, which reports it again
+    const unsigned stale = 1u;
+    if (c->d.use_lists && (f[FLAG_DIP_OVF] || f[FLAG_LIST_OVF]))
+      HIPC(hipMemcpy(c->d.rebuild + 3, &stale, sizeof(stale), hipMemcpyHostToDevice));
     if (f[FLAG_NONFINITE]) return fail(ROD_E_NONFINITE, "non-finite force, torque or position");
     if (f[FLAG_CONTACT_RANGE])
       return fail(ROD_E_OVERFLOW, "a contact pair's force, torque or energy was non-finite or "
