@@ -40,12 +40,14 @@ struct AdjPub {
   double *Fe, *Te, *h, *mu;
 };
 
-// Second moment planes and the shape of the fused steps (k_step.hip), when the
-// forward takes them (mu null otherwise).
+// The fused steps (k_step.hip) when the forward takes them: second moment planes of one
+// launch per step (null otherwise), or the largest member of many steps per launch (0
+// otherwise).
 struct TapeSmall {
   double* mu = nullptr;
   float* muf = nullptr;
-  int many = 0;  // members fit the many-steps kernel: their largest size
+  int many = 0;
+  bool fused() const { return mu || many; }
 };
 
 struct Tape {

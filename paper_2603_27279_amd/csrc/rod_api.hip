@@ -65,8 +65,9 @@ struct rod_ctx {
   std::vector<void*> plan_allocs;   // dipole work list, slot counts, partial slots
   std::vector<int> mrange_h;        // [2M] member particle ranges
   int max_member = 0;               // particles of the largest member
-  // Second set of state planes (x, v, q, w as in a recorded state, then moments)
-  // of the fused steps of small systems, or null.
+  // How the small-member layout's steps run (small_form), and the second set of state
+  // planes (x, v, q, w as in a recorded state, then moments) of the fused ones, or null.
+  int form = 0;
   double* alt = nullptr;
   double* halo = nullptr;  // Dev::halo of the fused bond and kick pass, or null
   float* alt_muf = nullptr;
@@ -386,6 +387,49 @@ static void dipole_ranges(const rod_ctx* c, int m, F&& f) {
   }
 }
 
+// Steps of the small-member layout: as forces and kick (FORM_TWO), as one launch
+// (FORM_STEP, k_step) or many in a launch (FORM_MANY, k_steps).
+enum { FORM_TWO = 0, FORM_STEP, FORM_MANY };
+struct FormCase { bool mixed, dipole, contact, hm; long n; int members, max_member; };
+// k_step serves its targets by waves that scan the whole member for dipoles and contacts
+// alike, and a compute unit holds one of its workgroups at a time: 1024 particles (of
+// four per workgroup) or 4096 (of sixteen) make one round over the chip. Its scan beats
+// the cell search and a launch only in few rounds and short members. Largest member for
+// which it does, by particles and terms; ratios are time as two launches over time
+// fused, mixed / FP64, over members of 33 to 2048 of all sizes that the layout takes:
+//   - up to 1024 particles always (1.13 to 2.2);
+//   - dipoles alone: 4 x 1024 1.24 / 1.08, 2 x 2048 1.04 / 1.00; 32 x 200 1.24 / 1.13,
+//     8 x 768 0.94 / 0.87; past 8192 the FP64 arithmetic decides (128 x 96 1.18 / 1.05,
+//     256 x 33 1.06 / 0.89);
+//   - contact: rods packed at the contact distance, every particle touching four of
+//     others (spread out, the fused form gains 0.2 to 0.5 more). With dipoles 4 x 1024 1.09 / 1.00,
+//     16 x 512 0.85 / 0.85, 1 x 2048 0.72 / 0.74, 500 x 64 1.41 / 1.26, 100 x 200 0.83;
+//     alone 16 x 256 1.07 / 1.03, 8 x 512 0.81 / 0.79, 16 x 512 0.54 / 0.52;
+//   - Hertz-Mindlin: 16 x 256 0.98 / 1.00 (spread out 1.6 / 1.5), 8 x 512 0.73 / 0.72;
+//     with dipoles 16 x 256 1.21 / 1.20, 64 x 96 0.80 / 0.77;
+//   - neither dipoles nor contact: the scan is for nothing (16 x 256 1.13 / 1.07,
+//     1 x 2048 0.57 / 0.56, 100 x 200 0.36).
+static int fused_member_max(const FormCase& f) {
+  //                    particles up to   2048  4096  8192 16384 more
+  static const int by_terms[2][3][5] = {{{   0,  256,    0,    0,  0},    // neither
+                                         { 256,  256,   64,    0,  0},    // Hookean contact
+                                         { 256,  256,   64,    0,  0}},   // Hertz-Mindlin
+                                        {{1024, 1024,  256,  128,  0},    // dipoles
+                                         { 256, 1024,  256,  128, 64},    // and Hookean contact
+                                         { 256,  256,   64,   64, 64}}};  // and Hertz-Mindlin
+  if (f.n <= 1024) return 1024;
+  const int band = f.n <= 2048 ? 0 : f.n <= 4096 ? 1 : f.n <= 8192 ? 2 : f.n <= 16384 ? 3 : 4;
+  const int m = by_terms[f.dipole][!f.contact ? 0 : f.hm ? 2 : 1][band];
+  return f.dipole && !f.contact && band == 3 && !f.mixed ? 0 : m;
+}
+// k_steps takes every system of members it can hold (also 4,000 of 16 with dipoles: 95
+// us as two launches, 52), but with neither dipoles nor contact the two launches' time
+// does not grow with the members (10.5 us), and its own does by 3.1 us per 256 of them.
+static int small_form(const FormCase& f) {
+  if (!f.hm && f.max_member <= STEPS_MAX && (f.dipole || f.contact || f.members <= 768)) return FORM_MANY;
+  return f.max_member <= fused_member_max(f) ? FORM_STEP : FORM_TWO;
+}
+
 static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
   const std::vector<int>& mrange = c->mrange_h;
   const int M = c->desc.n_members;
@@ -475,7 +519,11 @@ static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
   c->max_member = max_member;
   c->alt = nullptr;
   c->alt_muf = nullptr;
-  if (small && c->d.dcut == 0.0 && !c->d.ew_on) {
+  c->form = FORM_TWO;
+  if (small && c->d.dcut == 0.0 && !c->d.ew_on && !c->d.use_lists)
+    c->form = small_form({c->desc.precision == ROD_MIXED, c->d.dipole_on != 0, c->d.contact_on != 0,
+                          c->d.hm != 0, N, M, max_member});
+  if (c->form == FORM_STEP) {
     TRY(palloc(c, &c->alt, (c->d.muf ? 18 : 16) * (size_t)N));  // and the FP32 moments
     if (c->d.muf) c->alt_muf = (float*)(c->alt + 16 * (size_t)N);
   }
@@ -719,15 +767,17 @@ static size_t workspace_bytes(const rod_desc* d, int max_slots) {
   if (d->dipole_on) b += 4 * N + 48 * ((N + 63) / 64);  // spatial order and its chunk boxes
   if (d->bond_damping) b += 8 * 4 * R + 8 * 2 * 5 * N;                       // bond damping
   b += 8 * energy_doubles(N, M) + 8 * 9 * M;                                                  // energy
-  if (!dcut && !(d->box[0] > 0)) {  // second state planes of the fused small steps
+  if (!dcut && !(d->dipole_on && d->box[0] > 0)) {  // second state planes of the fused small steps
     std::vector<long> size(M, 0);
-    long largest = 0;
-    for (size_t r = 0; r < R; ++r) {
-      long& m = size[d->rod_member[r]];
-      m += d->rod_offset[r + 1] - d->rod_offset[r];
-      largest = std::max(largest, m);
-    }
-    if (largest <= 2048) b += (8 * 16 + (d->precision == ROD_MIXED ? 12 : 0)) * N;
+    for (size_t r = 0; r < R; ++r) size[d->rod_member[r]] += d->rod_offset[r + 1] - d->rod_offset[r];
+    const long largest = *std::max_element(size.begin(), size.end());
+    const FormCase f{d->precision == ROD_MIXED, d->dipole_on != 0, d->contact_on != 0, hm,
+                     (long)N, (int)M, (int)largest};
+    long iblocks = 0;
+    for (long n : size) iblocks += (n + 63) / 64;
+    const bool lists = f.contact && f.n >= CONTACT_LANES_MAX_N;
+    if (largest <= 2048 && iblocks < 512 && !lists && small_form(f) == FORM_STEP)
+      b += 8 * (f.mixed ? 18 : 16) * N;
   }
   return b;
 }
@@ -790,17 +840,14 @@ struct NoRecord {
 // the level counter it reads alternates between step[1] and step[2]. Other
 // modes: pre, forces, post per step.
 // Whether rod_step takes the fused steps of small systems (k_step.hip): batched
-// launches of the small-member layout without a dipole cutoff, a box or contact
-// lists. A timed run takes the two-launch chain, whose kernels have classes of
-// their own; states are the same bits.
+// launches of the small-member layout where they are the faster form, without a dipole
+// cutoff, a box or contact lists. A timed run takes the two-launch chain, whose kernels
+// have classes of their own; states are the same bits.
 static bool small_steps(const rod_ctx* c) {
-  return c->launch_mode == ROD_LAUNCH_BATCHED && !c->timing && c->alt && !c->d.use_lists &&
-         !c->d.ibm_u;
+  return c->launch_mode == ROD_LAUNCH_BATCHED && !c->timing && c->form != FORM_TWO;
 }
 // Whether a launch serves many steps (a workgroup per member).
-static bool many_steps(const rod_ctx* c) {
-  return small_steps(c) && !c->d.hm && c->max_member <= STEPS_MAX;
-}
+static bool many_steps(const rod_ctx* c) { return small_steps(c) && c->form == FORM_MANY; }
 
 // n steps of a small system, a launch per STEPS_LAUNCH of them (a few milliseconds
 // each).
@@ -1648,10 +1695,11 @@ int rod_grad(rod_ctx* c, const rod_cotangent* gy, rod_gradients* gx) {
   TRY(enter(c));
   const bool cut = c->d.dcut > 0.0;
   TapeSmall small;
-  if (small_steps(c)) {
+  if (many_steps(c)) {
+    small.many = c->max_member;
+  } else if (small_steps(c)) {
     small.mu = c->alt + 13 * c->d.n;
     small.muf = c->alt_muf;
-    small.many = many_steps(c) ? c->max_member : 0;
   }
   TRY(adjoint_run(c->tape, c->d, c->desc.precision, cut ? c->adj_work : c->work,
                   cut ? c->adj_nwork : c->nwork, c->max_slots * c->d.parts, small, c->s, c->h_step, gy, gx));
