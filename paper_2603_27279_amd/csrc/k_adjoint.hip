@@ -1083,7 +1083,7 @@ int adjoint_run(Tape& t, const Dev& d, int precision, const DipWork* work, int n
   if (gy->w) ACHK(hipMemcpyAsync(a.cw, gy->w, b3, hipMemcpyDeviceToDevice, s));
   ACHK(hipMemsetAsync(a.mbbar, 0, b3, s));
   ACHK(hipMemsetAsync(a.fieldbar, 0, (size_t)d.field_len * d.M * 12 * sizeof(double), s));
-  if (small.fused() && !t.pub) {
+  if (small.reverse && !t.pub) {
     double* pub = nullptr;
     ATRY(adalloc(*t.allocs, &t.fieldc, (size_t)(t.every + 1) * 12 * N));
     ATRY(adalloc(*t.allocs, &t.fieldp, (size_t)(t.every + 1) * 12 * d.M));
@@ -1100,7 +1100,7 @@ int adjoint_run(Tape& t, const Dev& d, int precision, const DipWork* work, int n
     return ROD_OK;
   };
   auto undo = [&](int len) {
-    return small.fused() ? reverse_small(t, d, s, len)
+    return small.reverse ? reverse_small(t, d, s, len)
                     : reverse_segment(t, d, work, nwork, max_slots, s, len);
   };
   const int64_t nseg = (T + t.every - 1) / t.every;

@@ -42,12 +42,12 @@ struct AdjPub {
 
 // The fused steps (k_step.hip) when the forward takes them: second moment planes of one
 // launch per step (null otherwise), or the largest member of many steps per launch (0
-// otherwise).
+// otherwise); and whether the reverse takes its fused steps.
 struct TapeSmall {
   double* mu = nullptr;
   float* muf = nullptr;
   int many = 0;
-  bool fused() const { return mu || many; }
+  bool reverse = false;
 };
 
 struct Tape {

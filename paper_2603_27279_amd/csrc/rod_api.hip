@@ -430,6 +430,15 @@ static int small_form(const FormCase& f) {
   return f.max_member <= fused_member_max(f) ? FORM_STEP : FORM_TWO;
 }
 
+// Whether gradients of the small-member layout take one launch per reversed step
+// (k_adj_step): like k_step it scans whole members, from workgroups of four particles of
+// which a compute unit holds one at a time. Time of a gradient per step with two launches
+// per reversed step over that with one (FP64, dipoles / contact / neither): up to 1024
+// particles 1.07 to 1.5; 8 x 256 1.07 / 1.04 / 0.97 and 32 x 64 1.10 / 1.11 / 1.01; 4 x 512
+// 0.96 / 0.93 / 0.89, 1 x 2048 0.92 / 0.69 / 0.69; 16 x 256 0.84 / 0.77 / 0.71, 500 x 32
+// 0.56 / 0.49 / 0.38.
+static bool fused_reverse(long n, int max_member) { return n <= 1024 || (n <= 2048 && max_member <= 256); }
+
 static int build_dipole_plan(rod_ctx* c, int small_req, int target_wgs) {
   const std::vector<int>& mrange = c->mrange_h;
   const int M = c->desc.n_members;
@@ -1701,6 +1710,7 @@ int rod_grad(rod_ctx* c, const rod_cotangent* gy, rod_gradients* gx) {
     small.mu = c->alt + 13 * c->d.n;
     small.muf = c->alt_muf;
   }
+  small.reverse = small_steps(c) && fused_reverse(c->d.n, c->max_member);
   TRY(adjoint_run(c->tape, c->d, c->desc.precision, cut ? c->adj_work : c->work,
                   cut ? c->adj_nwork : c->nwork, c->max_slots * c->d.parts, small, c->s, c->h_step, gy, gx));
   TRY(leave(c));
