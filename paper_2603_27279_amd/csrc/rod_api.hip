@@ -1868,15 +1868,19 @@ extern "C" int rod_autotune(rod_ctx* c, const char* cache_path, int32_t force, c
       cands.push_back({0, 1024});
     }
     best_us = 1e300;
-    // split targets that give the same work list (in the same order) are timed once
-    std::vector<std::pair<int, int>> seen;
+    // split targets that give the same work list (in the same order) are timed once:
+    // layout, items, and the slots and parts that these are
+    struct List { int small, items, slots, parts; };
+    std::vector<List> seen;
     struct Timed { int small, target; double us; };
     std::vector<Timed> timed;
     for (const Cand& cd : cands) {
       TRY(build_dipole_plan(c, cd.small, cd.target));
       if (cd.small != 1) {
-        const std::pair<int, int> k{cd.small, c->nwork};
-        if (std::find(seen.begin(), seen.end(), k) != seen.end()) continue;
+        const List k{cd.small, c->nwork, c->max_slots, c->d.parts};
+        if (std::any_of(seen.begin(), seen.end(), [&](const List& l) {
+              return l.small == k.small && l.items == k.items && l.slots == k.slots && l.parts == k.parts;
+            })) continue;
         seen.push_back(k);
       }
       double us = 0.0;
