@@ -333,9 +333,11 @@ int rod_kernel_times(rod_ctx* c, double* ms, int64_t* launches);
  * targets per workgroup; members of at most 16384 particles), then the split
  * layout in particle order and in spatial order (64 targets per workgroup,
  * each member's sources split into enough ranges to give the launch 512 ...
- * 32768 work items; distinct work lists are timed once). Each candidate is
- * timed with HIP events on the library's stream over repeated force
- * evaluations at the current state (the state is not changed); the fastest is
+ * 32768 work items; distinct work lists are timed once). Without dipoles, below
+ * 65536 particles: the small-member layout and one split layout, in which steps
+ * run as other launches. Each candidate is timed with HIP events on the library's
+ * stream over steps of a copy of the current state (the state is not changed),
+ * launched as rod_step would launch them; the fastest is
  * applied, candidates within 1% of it counting as equal (the first of them in
  * the order above wins, so that timing noise does not flip the choice). With a
  * non-NULL cache_path (a JSON-lines file) the choice is looked up first

@@ -1746,31 +1746,97 @@ static void drop_graphs(rod_ctx* c) {
   tape_release(c->tape);
 }
 
-// Microseconds per force evaluation (pre, forces, gather) of the current layout.
-static int time_eval(rod_ctx* c, double* us) {
-  double* F = c->epart;  // scratch: [3N] force and [3N] torque
-  double* T = c->epart + 3 * c->d.n;
+namespace {
+struct TmpDev {  // device memory of one call
+  void* p = nullptr;
+  ~TmpDev() { if (p) (void)hipFree(p); }
+};
+
+// While it lives, the context steps a copy of its state (x, v, q, w, F, T and the level)
+// in `mem`, untimed, without recording histories and with error flags of its own. The
+// work buffers and lists are the context's: every call sets what it reads of them.
+constexpr size_t TRIAL_TAIL = 64;  // bytes of counters and flags behind the planes
+struct TrialState {
+  rod_ctx* c;
+  Dev own;
+  bool timing;
+  TrialState(rod_ctx* ctx, void* mem) : c(ctx), own(ctx->d), timing(ctx->timing) {
+    const long N = own.n;
+    Dev& d = c->d;
+    double* p = (double*)mem;
+    d.x = p; d.v = p + 3 * N; d.q = p + 6 * N; d.w = p + 10 * N; d.F = p + 13 * N; d.T = p + 16 * N;
+    d.step = (long long*)(p + 19 * N);
+    d.left = (unsigned*)(d.step + 3);
+    d.flags = (unsigned*)(d.step + 4);
+    static_assert(4 * sizeof(long long) + FLAG_COUNT * sizeof(unsigned) <= TRIAL_TAIL, "trial counters");
+    d.hist_write = 0;
+    c->timing = false;
+  }
+  ~TrialState() {
+    c->d = own;
+    c->timing = timing;
+  }
+  int reset() {  // the copy, from the context's state
+    const size_t p = own.n * sizeof(double);
+    const struct { double* to; const double* from; int planes; } parts[] = {
+        {c->d.x, own.x, 3}, {c->d.v, own.v, 3}, {c->d.q, own.q, 4},
+        {c->d.w, own.w, 3}, {c->d.F, own.F, 3}, {c->d.T, own.T, 3}};
+    for (const auto& a : parts) HIPC(hipMemcpyAsync(a.to, a.from, a.planes * p, hipMemcpyDeviceToDevice, c->s));
+    HIPC(hipMemcpyAsync(c->d.step, own.step, 4 * sizeof(long long), hipMemcpyDeviceToDevice, c->s));
+    HIPC(launch_fill_i32((int*)c->d.flags, FLAG_COUNT, 0, c->s));
+    return ROD_OK;
+  }
+};
+}  // namespace
+
+// Whether the choice of the dipole layout is one of how steps run: with an all-pairs sum,
+// and without dipoles in systems small enough for fused steps.
+static bool layout_matters(const rod_ctx* c) {
+  if (c->d.dipole_on) return c->d.dcut == 0.0 && !c->d.ew_on;
+  return c->max_member <= 16384 && c->d.n < CONTACT_LANES_MAX_N;
+}
+
+// Microseconds per step of the current layout, by the launches that rod_step would make
+// of it (the fused steps of small systems among them), on a copy of the state in `trial`;
+// per force evaluation (pre, forces, gather) where the layout does not matter.
+static int time_eval(rod_ctx* c, void* trial, double* us) {
   NoRecord keep(c);
-  auto eval = [&]() -> int {
-    HIPC(launch_pre(c->d, PRE_EVAL, c->s));
-    TRY(force_terms(c, 0));
-    HIPC(launch_post(c->d, POST_EVAL, ROD_TERM_ALL, F, T, nullptr, c->s));
+  auto evals = [&](int n) -> int {
+    double* F = c->epart;  // scratch: [3N] force and [3N] torque
+    for (int k = 0; k < n; ++k) {
+      HIPC(launch_pre(c->d, PRE_EVAL, c->s));
+      TRY(force_terms(c, 0));
+      HIPC(launch_post(c->d, POST_EVAL, ROD_TERM_ALL, F, F + 3 * c->d.n, nullptr, c->s));
+    }
+    return ROD_OK;
+  };
+  auto run = [&](hipEvent_t a, hipEvent_t b, int reps) -> int {
+    if (!layout_matters(c)) {
+      if (a) HIPC(hipEventRecord(a, c->s));
+      TRY(evals(reps));
+    } else {
+      TrialState t(c, trial);
+      TRY(t.reset());
+      if (a) HIPC(hipEventRecord(a, c->s));
+      TRY(many_steps(c) ? enqueue_many(c, reps) : enqueue_steps(c, reps));
+    }
+    if (b) HIPC(hipEventRecord(b, c->s));
     return ROD_OK;
   };
   hipEvent_t a, b;
   HIPC(hipEventCreate(&a));
   HIPC(hipEventCreate(&b));
-  int rc = ROD_OK;
   float ms = 0.f;
   int reps = 3;
-  for (int k = 0; k < 3 && rc == ROD_OK; ++k) rc = eval();  // warm-up
+  int rc = run(nullptr, nullptr, 3);  // warm-up
   for (int round = 0; round < 2 && rc == ROD_OK; ++round) {
-    if (hipEventRecord(a, c->s) != hipSuccess) { rc = fail(ROD_E_HIP, "event record failed"); break; }
-    for (int k = 0; k < reps && rc == ROD_OK; ++k) rc = eval();
+    rc = run(a, b, reps);
     if (rc != ROD_OK) break;
-    if (hipEventRecord(b, c->s) != hipSuccess || hipEventSynchronize(b) != hipSuccess ||
-        hipEventElapsedTime(&ms, a, b) != hipSuccess) { rc = fail(ROD_E_HIP, "event timing failed"); break; }
-    // aim at ~5 ms of timed work (at most 200 evaluations)
+    if (hipEventSynchronize(b) != hipSuccess || hipEventElapsedTime(&ms, a, b) != hipSuccess) {
+      rc = fail(ROD_E_HIP, "event timing failed");
+      break;
+    }
+    // aim at ~5 ms of timed work (at most 200 steps)
     const double per = std::max(1e-3, (double)ms / reps);
     if (round == 0) reps = (int)std::min(200.0, std::max(3.0, 5.0 / per));
   }
@@ -1857,16 +1923,16 @@ extern "C" int rod_autotune(rod_ctx* c, const char* cache_path, int32_t force, c
   if (!cached) {
     struct Cand { int small, target; };
     std::vector<Cand> cands;
-    int max_member = 0;
-    for (size_t k = 0; k + 1 < c->mrange_h.size(); k += 2)
-      max_member = std::max(max_member, c->mrange_h[k + 1] - c->mrange_h[k]);
-    if (c->desc.dipole_on && c->d.dcut == 0.0 && !c->d.ew_on) {  // (a cutoff or a box: no layout)
-      if (max_member <= 16384) cands.push_back({1, 0});
+    if (layout_matters(c) && c->max_member <= 16384) cands.push_back({1, 0});
+    if (layout_matters(c) && c->d.dipole_on) {
       for (int sp : {0, 2})  // particle order, spatial order
         for (int t : {512, 1024, 2048, 4096, 8192, 16384, 32768}) cands.push_back({sp, t});
     } else {
       cands.push_back({0, 1024});
     }
+    TmpDev trial;
+    HIPC(hipMalloc(&trial.p, 19 * sizeof(double) * (size_t)c->d.n + TRIAL_TAIL));
+    HIPC(hipMemset(trial.p, 0, 19 * sizeof(double) * (size_t)c->d.n + TRIAL_TAIL));
     best_us = 1e300;
     // split targets that give the same work list (in the same order) are timed once:
     // layout, items, and the slots and parts that these are
@@ -1884,7 +1950,7 @@ extern "C" int rod_autotune(rod_ctx* c, const char* cache_path, int32_t force, c
         seen.push_back(k);
       }
       double us = 0.0;
-      TRY(time_eval(c, &us));
+      TRY(time_eval(c, trial.p, &us));
       char line[160];
       snprintf(line, sizeof(line), "%s target_wgs=%d work_items=%d slots=%d: %.2f us/eval\n",
                layout_name(cd.small), cd.target, c->nwork, c->max_slots, us);
@@ -1926,13 +1992,6 @@ extern "C" int rod_autotune(rod_ctx* c, const char* cache_path, int32_t force, c
 }
 
 // ------------------------------------------------------------------ ramp
-namespace {
-struct TmpDev {  // device memory of one call
-  void* p = nullptr;
-  ~TmpDev() { if (p) (void)hipFree(p); }
-};
-}  // namespace
-
 // Rods immersed in a lattice (Methods, "Immersed boundary coupling"). Per
 // cycle: the lattice's velocity interpolated at every particle, then n_sub rod steps
 // whose gather adds the penalty force and records it, with the spreading of
