@@ -775,26 +775,31 @@ __global__ __launch_bounds__(64 * (ADJ_T + 2)) void k_adj_step(Dev d, Adj a, Adj
 }
 static_assert(11 * (ADJ_T + 1) <= 64, "a lane per bond column");
 
-// Field gradient of a segment: the member sums of every level (a workgroup each),
-// then their addition to the table's rows, latest level first.
-__global__ __launch_bounds__(256) void k_adj_field_sums(Dev d, const double* fieldc, double* part) {
+// Field gradient of a segment of len levels: the member sums of every level (a workgroup
+// each, levels past the grid's height in turn), then their addition to the table's rows,
+// latest level first.
+__global__ __launch_bounds__(256) void k_adj_field_sums(Dev d, const double* fieldc, double* part,
+                                                        int len) {
   __shared__ double red[12][256];
-  const int mem = blockIdx.x, koff = 1 + blockIdx.y;
+  const int mem = blockIdx.x;
   const int b = d.mrange[2 * mem], e = d.mrange[2 * mem + 1];
   const long N = d.n;
-  const double* f = fieldc + (long)koff * 12 * N;
-  double s[12];
-  for (int k = 0; k < 12; ++k) s[k] = 0.0;
-  for (int i = b + threadIdx.x; i < e; i += blockDim.x)
-    for (int k = 0; k < 12; ++k) s[k] += f[k * N + i];
-  for (int k = 0; k < 12; ++k) red[k][threadIdx.x] = s[k];
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-      for (int k = 0; k < 12; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
+  for (long koff = 1 + blockIdx.y; koff <= len; koff += gridDim.y) {
+    const double* f = fieldc + koff * 12 * N;
+    double s[12];
+    for (int k = 0; k < 12; ++k) s[k] = 0.0;
+    for (int i = b + threadIdx.x; i < e; i += blockDim.x)
+      for (int k = 0; k < 12; ++k) s[k] += f[k * N + i];
+    for (int k = 0; k < 12; ++k) red[k][threadIdx.x] = s[k];
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+      if ((int)threadIdx.x < w)
+        for (int k = 0; k < 12; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
+      __syncthreads();
+    }
+    if (threadIdx.x < 12) part[(koff * d.M + mem) * 12 + threadIdx.x] = red[threadIdx.x][0];
     __syncthreads();
   }
-  if (threadIdx.x < 12) part[((long)koff * d.M + mem) * 12 + threadIdx.x] = red[threadIdx.x][0];
 }
 __global__ __launch_bounds__(64) void k_adj_field_rows(Dev d, Adj a, const double* __restrict__ part,
                                                        double* __restrict__ bar, int len) {
@@ -1039,8 +1044,9 @@ static int reverse_small(Tape& t, const Dev& d, hipStream_t s, int len) {
                        t.fieldc + (size_t)(k - 1) * 12 * N);
     ACHK(hipGetLastError());
   }
-  hipLaunchKernelGGL(k_adj_field_sums, dim3(d.M, len), dim3(256), 0, s, d, (const double*)t.fieldc,
-                     t.fieldp);
+  // (a grid is at most 65,535 high; 16,384 workgroups fill the chip many times over)
+  hipLaunchKernelGGL(k_adj_field_sums, dim3(d.M, std::min(len, 16384)), dim3(256), 0, s, d,
+                     (const double*)t.fieldc, t.fieldp, len);
   ACHK(hipGetLastError());
   hipLaunchKernelGGL(k_adj_field_rows, dim3(nblk(12 * d.M, 64)), dim3(64), 0, s, d, a,
                      (const double*)t.fieldp, a.fieldbar, len);
