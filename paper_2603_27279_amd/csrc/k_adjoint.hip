@@ -1074,6 +1074,28 @@ void tape_release(Tape& t) {
   t.g_recompute = t.g_reverse = nullptr;
 }
 
+// The buffers of the fused reverse steps, at their first use; false where they do not fit
+// in memory (they add up to 55% to a tape: the reverse then takes two launches per step).
+static bool fused_buffers(Tape& t, const Dev& d) {
+  if (t.pub) return true;
+  const size_t N = d.n, levels = (size_t)t.every + 1;
+  // Jacobians of as many levels as fit in 128 MiB (at least one)
+  const size_t jl = std::max<size_t>(1, std::min<size_t>(t.every, (128u << 20) / (99 * sizeof(double) * N)));
+  const size_t count = 12 * levels * (N + d.M) + 99 * jl * N + 12 * N;
+  void* q = nullptr;
+  if (hipMalloc(&q, count * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  t.allocs->push_back(q);
+  t.fieldc = (double*)q;
+  t.fieldp = t.fieldc + 12 * levels * N;
+  t.jac = t.fieldp + 12 * levels * d.M;
+  t.jac_levels = (int)jl;
+  t.pub = t.jac + 99 * jl * N;
+  return true;
+}
+
 int adjoint_run(Tape& t, const Dev& d, int precision, const DipWork* work, int nwork,
                 int max_slots, const TapeSmall& small, hipStream_t s, int64_t end_step,
                 const rod_cotangent* gy, rod_gradients* gx) {
@@ -1089,16 +1111,7 @@ int adjoint_run(Tape& t, const Dev& d, int precision, const DipWork* work, int n
   if (gy->w) ACHK(hipMemcpyAsync(a.cw, gy->w, b3, hipMemcpyDeviceToDevice, s));
   ACHK(hipMemsetAsync(a.mbbar, 0, b3, s));
   ACHK(hipMemsetAsync(a.fieldbar, 0, (size_t)d.field_len * d.M * 12 * sizeof(double), s));
-  if (small.reverse && !t.pub) {
-    double* pub = nullptr;
-    ATRY(adalloc(*t.allocs, &t.fieldc, (size_t)(t.every + 1) * 12 * N));
-    ATRY(adalloc(*t.allocs, &t.fieldp, (size_t)(t.every + 1) * 12 * d.M));
-    // Jacobians of as many levels as fit in 128 MiB (at least one)
-    t.jac_levels = (int)std::max<size_t>(1, std::min<size_t>(t.every, (128u << 20) / (99 * sizeof(double) * N)));
-    ATRY(adalloc(*t.allocs, &t.jac, (size_t)t.jac_levels * 99 * N));
-    ATRY(adalloc(*t.allocs, &pub, 12 * (size_t)N));
-    t.pub = pub;
-  }
+  const bool fused_reverse = small.reverse && fused_buffers(t, d);
   auto redo = [&](int len, int64_t s0) -> int {
     if (!small.many) return recompute(t, d, precision, work, nwork, small, s, len);
     Dev v = view(d, t.seg, a.level);
@@ -1106,7 +1119,7 @@ int adjoint_run(Tape& t, const Dev& d, int precision, const DipWork* work, int n
     return ROD_OK;
   };
   auto undo = [&](int len) {
-    return small.reverse ? reverse_small(t, d, s, len)
+    return fused_reverse ? reverse_small(t, d, s, len)
                     : reverse_segment(t, d, work, nwork, max_slots, s, len);
   };
   const int64_t nseg = (T + t.every - 1) / t.every;

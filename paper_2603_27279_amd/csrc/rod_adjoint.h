@@ -59,7 +59,7 @@ struct Tape {
   Adj a{};
   // graphs of one full segment: recompute and reverse (captured on first use)
   hipGraphExec_t g_recompute = nullptr, g_reverse = nullptr;
-  // fused reverse steps of small systems, allocated at their first use: the second
+  // fused reverse steps of small systems, one block allocated at their first use: the second
   // published set, every level's contributions to the field gradient and their sums,
   // the bond Jacobians of up to jac_levels levels
   std::vector<void*>* allocs = nullptr;
