@@ -125,8 +125,9 @@ __device__ __forceinline__ V3<double> pre_particle(const Dev& d, long i, int mod
     if (d.use_lists) {
       const V3<double> m = x - ld3(d.xb, N, i);
       const double lim = NBR_MOVE * d.skin;
-      // (positions the caller has changed count too)
-      const bool far = d.rebuild[3] != 0u || !(dot(m, m) <= lim * lim);
+      // (positions the caller has changed count too; particle 0 speaks for a mark, or
+      // every wave's atomic would meet at the flag)
+      const bool far = !(dot(m, m) <= lim * lim) || (i == 0 && d.rebuild[3] != 0u);
       const unsigned long long who = __ballot(far);
       if (far && __lane_id() == (unsigned)(__ffsll((long long)who) - 1))
         atomicOr(&d.rebuild[d.lc & 1], 1u);
