@@ -58,11 +58,12 @@ __device__ __forceinline__ void advance_particle(const Dev& d, int b, long long 
 // rotation of driven ones. The result goes to the planes of d.nx when set,
 // else in place; states of particles that do not move are written only when
 // `copy_still` is set (out-of-place step). A particle too far from its place at the
-// last list build sets rebuild[flag], the entry of the coming force evaluation.
+// last list build sets rebuild[flag], the entry of the coming force evaluation (unless
+// `check` is off: the caller looks itself).
 __device__ __forceinline__ void advance(const Dev& d, long i, int b, long long lvl, V3<double>& x,
                                         V3<double>& v, Q4<double>& q, V3<double>& w,
                                         V3<double> F, V3<double> T, double minv, double Iinv,
-                                        bool copy_still, int flag) {
+                                        bool copy_still, int flag, bool check = true) {
   const long N = d.n;
   // output planes: those of the next recorded state, or in place
   double* const xo = d.nx ? d.nx : d.x;
@@ -71,7 +72,7 @@ __device__ __forceinline__ void advance(const Dev& d, long i, int b, long long l
   double* const wo = d.nx ? d.nx + 10 * N : d.w;
   advance_particle(d, b, lvl, x, v, q, w, F, T, minv, Iinv);
   if (b == 0) {
-    if (d.use_lists) {  // moved too far since the contact lists were built?
+    if (d.use_lists && check) {  // moved too far since the contact lists were built?
       const V3<double> m = x - ld3(d.xb, N, i);
       const double lim = NBR_MOVE * d.skin;
       const bool far = dot(m, m) > lim * lim;

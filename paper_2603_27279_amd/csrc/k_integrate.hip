@@ -103,7 +103,7 @@ __device__ __forceinline__ V3<double> pre_particle(const Dev& d, long i, int mod
   if (mode == PRE_STEP) {
     V3<double> v = ld3(sv, N, i), w = ld3(sw, N, i);
     advance(d, i, b, lvl, x, v, q, w, ld3(sF, N, i), ld3(sT, N, i), d.minv[i], d.Iinv[i],
-            d.src != nullptr || d.nx != nullptr, d.lc & 1);
+            d.src != nullptr || d.nx != nullptr, d.lc & 1, d.halo == nullptr);
     vh = v;
   } else if (mode == PRE_PREPARE) {
     q = qnormalize(q);
