@@ -355,11 +355,13 @@ int rod_autotune(rod_ctx* c, const char* cache_path, int32_t force, char* report
  * timed as ROD_KERNEL_CONTACT); between two consecutive steps of one call the
  * closing half-kick and the next step's opening half-kick, drift and rotation
  * share one launch. In the small-member dipole layout a whole step is one
- * launch, and members of at most 32 particles (without Hertz-Mindlin contact)
- * take many steps per launch, whatever graph_steps says. Without an all-pairs
+ * launch where that is faster (up to 1024 particles; beyond, by the members' size
+ * and the force terms), and members of at most 32 particles (without Hertz-Mindlin
+ * contact) take many steps per launch, whatever graph_steps says. Without an all-pairs
  * dipole sum, large systems (and all with a dipole cutoff) evaluate the bonds in
  * the fused half-kick launch; their candidate lists then outlive a call (each call
- * checks every position against the last build's first).
+ * checks every position against the last build's first, and whether anything else
+ * has built lists since).
  * ROD_LAUNCH_SEPARATE: as batched, with the three force terms launched as
  * separate kernels and no kick fusion (per-term timing).
  * ROD_LAUNCH_PER_ROD: the plain per-rod loop, every kernel launched once per

@@ -185,10 +185,11 @@ __device__ __forceinline__ void contact_thread(const Dev& d, long blk) {
 
 // Contact force of a large system from per-particle candidate lists (Verlet
 // lists with a skin). A list holds every non-excluded particle of the member
-// closer than r_c + skin when it was built. It is rebuilt from the cells at the
-// first step of every rod_step call and whenever some particle has moved more
-// than NBR_MOVE * skin since the last build; the displacement check runs where
-// particles move. Between builds every pair closer than r_c is still listed, so
+// closer than r_c + skin when it was built. It is rebuilt from the cells whenever
+// some particle has moved more than NBR_MOVE * skin since the last build; the
+// displacement check runs where particles move. Across calls, the chain of the fused
+// bond and kick pass keeps its lists (its opening kernel looks at every position and
+// at Dev::rebuild[3]); other chains rebuild at the first step of a call. Between builds every pair closer than r_c is still listed, so
 // the exact selection r^2 < r_c^2 and the fixed-point sums give the cell
 // search's result bit for bit, while a step reads a short contiguous list
 // instead of 27 scattered cells. A particle with more than NBR_CAP candidates

@@ -3,8 +3,8 @@
 // particles j of its member with r^2 = (dx dx + dy dy) + dz dz < dcut^2 (exact
 // FP64 selection, as in the contact search), through the same pair law as the
 // all-pairs sum. Each particle keeps a Verlet list of the member's particles
-// closer than dcut + skin, rebuilt with the contact lists (first step of a
-// call, or when a particle has moved more than NBR_MOVE * skin).
+// closer than dcut + skin, rebuilt with the contact lists (see
+// contact_listed).
 //
 // A rebuild first sorts the particles by cell (cells of side dcut + skin, so a
 // particle's candidates lie in the 3 x 3 x 3 cells around its own). A cell's

@@ -22,6 +22,9 @@
 // members of 200, mixed: 28 -> 17.5 us. k_steps takes members of up to 32
 // particles: its few dipole waves need a round per handful of targets, 4.2 us at
 // 32, 7.8 at 48 and 9.9 at 64, where k_step takes 7.0 to 7.6 at any of these.
+// A compute unit holds one workgroup of either kernel at a time (160 and more registers
+// in 5 or 9 waves, 224 and more in 8), so their time grows by the round of workgroups
+// over the chip; which systems take them is small_form's (rod_api.hip).
 #include <type_traits>
 
 #include "rod.h"
@@ -188,7 +191,8 @@ __global__ __launch_bounds__(64 * (NW + 1)) void k_step(Dev d, StepOut o) {
 // a particle has lives in LDS and is read where it is used: held in registers
 // across the loop, beside the bond's and the update's temporaries, it spilled
 // (eight waves leave 256 registers each; with sixteen and 128 the spills cost
-// more than the waves gain: N = 20 FP64 6.7 us per step against 3.5).
+// more than the waves gain: N = 20 FP64 6.7 us per step against 3.5). The FP64 forms
+// still spill 12 to 28 bytes per lane, the mixed ones nothing.
 constexpr int STEPS_THREADS = 512;
 struct StepsSmem {
   double x[3 * STEPS_MAX], q[4 * STEPS_MAX], v[3 * STEPS_MAX], w[3 * STEPS_MAX];

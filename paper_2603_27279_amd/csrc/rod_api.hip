@@ -858,8 +858,8 @@ static bool small_steps(const rod_ctx* c) {
 // Whether a launch serves many steps (a workgroup per member).
 static bool many_steps(const rod_ctx* c) { return small_steps(c) && c->form == FORM_MANY; }
 
-// n steps of a small system, a launch per STEPS_LAUNCH of them (a few milliseconds
-// each).
+// n steps of a small system, a launch per STEPS_LAUNCH of them (a few milliseconds for
+// up to 256 members, which run side by side; 50 for 4,000).
 constexpr int STEPS_LAUNCH = 1000;
 static int enqueue_many(rod_ctx* c, int64_t n) {
   for (int64_t k = 0; k < n; k += STEPS_LAUNCH)
