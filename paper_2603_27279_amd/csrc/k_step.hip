@@ -22,9 +22,10 @@
 // members of 200, mixed: 28 -> 17.5 us. k_steps takes members of up to 32
 // particles: its few dipole waves need a round per handful of targets, 4.2 us at
 // 32, 7.8 at 48 and 9.9 at 64, where k_step takes 7.0 to 7.6 at any of these.
-// A compute unit holds one workgroup of either kernel at a time (160 and more registers
-// in 5 or 9 waves, 224 and more in 8), so their time grows by the round of workgroups
-// over the chip; which systems take them is small_form's (rod_api.hip).
+// Their time grows once every compute unit has a workgroup: two of the five-wave ones
+// share a unit (160 to 168 registers, three waves per SIMD), the nine-wave ones and those
+// of k_steps (224 registers and more) wait for it. Which systems take them is
+// small_form's (rod_api.hip).
 #include <type_traits>
 
 #include "rod.h"

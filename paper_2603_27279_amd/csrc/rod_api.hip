@@ -392,10 +392,10 @@ static void dipole_ranges(const rod_ctx* c, int m, F&& f) {
 enum { FORM_TWO = 0, FORM_STEP, FORM_MANY };
 struct FormCase { bool mixed, dipole, contact, hm; long n; int members, max_member; };
 // k_step serves its targets by waves that scan the whole member for dipoles and contacts
-// alike, and a compute unit holds one of its workgroups at a time: 1024 particles (of
-// four per workgroup) or 4096 (of sixteen) make one round over the chip. Its scan beats
-// the cell search and a launch only in few rounds and short members. Largest member for
-// which it does, by particles and terms; ratios are time as two launches over time
+// alike. 1024 particles (four per workgroup) or 4096 (sixteen, past 2048) give every
+// compute unit one workgroup; further ones share a unit or wait for it. Its scan beats
+// the cell search and a launch only up to little more than that and in short members.
+// Largest member for which it does, by particles and terms; ratios are time as two launches over time
 // fused, mixed / FP64, over members of 33 to 2048 of all sizes that the layout takes:
 //   - up to 1024 particles always (1.13 to 2.2);
 //   - dipoles alone: 4 x 1024 1.24 / 1.08, 2 x 2048 1.04 / 1.00; 32 x 200 1.24 / 1.13,
@@ -431,8 +431,8 @@ static int small_form(const FormCase& f) {
 }
 
 // Whether gradients of the small-member layout take one launch per reversed step
-// (k_adj_step): like k_step it scans whole members, from workgroups of four particles of
-// which a compute unit holds one at a time. Time of a gradient per step with two launches
+// (k_adj_step): like k_step it scans whole members, from workgroups of four particles, one
+// for every compute unit at 1024. Time of a gradient per step with two launches
 // per reversed step over that with one (FP64, dipoles / contact / neither): up to 1024
 // particles 1.07 to 1.5; 8 x 256 1.07 / 1.04 / 0.97 and 32 x 64 1.10 / 1.11 / 1.01; 4 x 512
 // 0.96 / 0.93 / 0.89, 1 x 2048 0.92 / 0.69 / 0.69; 16 x 256 0.84 / 0.77 / 0.71, 500 x 32
