@@ -313,11 +313,14 @@ __device__ __forceinline__ void dipole_small_item(const Dev& d, const DipWork& w
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
+      // In FP64 a source past the end takes part with 1/r = 0, which adds zeros: a branch
+      // around each pair keeps the four chains apart, 10.2 against 8.1 us for 1024 targets
+      // (8.0 with the two Newton steps that the reciprocal root took before).
       const int j = jb + 64 * u;
-      if (j >= wk.j1) break;
+      if (sizeof(R) == 4 && j >= wk.j1) break;
       const R dx = (R)(xi - sx[u]), dy = (R)(yi - sy[u]), dz = (R)(zi - sz[u]);
       const R r2 = fma_(dz, dz, fma_(dy, dy, dx * dx));
-      const R rinv = (j == i) ? R(0) : rsq(r2);
+      const R rinv = (j == i || j >= wk.j1) ? R(0) : rsq(r2);
       pair_acc(dx, dy, dz, smx[u], smy[u], smz[u], mix, miy, miz, rinv, m5, A);
     }
   }
