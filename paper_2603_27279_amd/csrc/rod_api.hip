@@ -398,15 +398,16 @@ struct FormCase { bool mixed, dipole, contact, hm; long n; int members, max_memb
 // Largest member for which it does, by particles and terms; ratios are time as two launches over time
 // fused, mixed / FP64, over members of 33 to 2048 of all sizes that the layout takes:
 //   - up to 1024 particles always (1.13 to 2.2);
-//   - dipoles alone: 4 x 1024 1.24 / 1.08, 2 x 2048 1.04 / 1.00; 32 x 200 1.24 / 1.13,
-//     8 x 768 0.94 / 0.87; past 8192 the FP64 arithmetic decides (128 x 96 1.18 / 1.05,
-//     256 x 33 1.06 / 0.89);
+//   - dipoles alone: 4 x 1024 1.24 / 1.07, 2 x 2048 1.04 / 0.98; 32 x 200 1.24 / 1.07,
+//     8 x 768 0.94 / 0.83; past 8192 the FP64 arithmetic decides (128 x 96 1.18 / 1.10,
+//     128 x 128 1.09 / 1.01, 500 x 33 0.99 / 0.88);
 //   - contact: rods packed at the contact distance, every particle touching four of
-//     others (spread out, the fused form gains 0.2 to 0.5 more). With dipoles 4 x 1024 1.09 / 1.00,
-//     16 x 512 0.85 / 0.85, 1 x 2048 0.72 / 0.74, 500 x 64 1.41 / 1.26, 100 x 200 0.83;
+//     others (spread out, the fused form gains 0.2 to 0.5 more). With dipoles 4 x 768
+//     1.03 / 0.92, 16 x 512 0.85 / 0.81, 1 x 2048 0.72 / 0.71, 500 x 64 1.41 / 1.28,
+//     100 x 200 0.83 / 0.78;
 //     alone 16 x 256 1.07 / 1.03, 8 x 512 0.81 / 0.79, 16 x 512 0.54 / 0.52;
 //   - Hertz-Mindlin: 16 x 256 0.98 / 1.00 (spread out 1.6 / 1.5), 8 x 512 0.73 / 0.72;
-//     with dipoles 16 x 256 1.21 / 1.20, 64 x 96 0.80 / 0.77;
+//     with dipoles 16 x 256 1.21 / 1.18, 64 x 96 0.80 / 0.78;
 //   - neither dipoles nor contact: the scan is for nothing (16 x 256 1.13 / 1.07,
 //     1 x 2048 0.57 / 0.56, 100 x 200 0.36).
 static int fused_member_max(const FormCase& f) {
@@ -420,7 +421,8 @@ static int fused_member_max(const FormCase& f) {
   if (f.n <= 1024) return 1024;
   const int band = f.n <= 2048 ? 0 : f.n <= 4096 ? 1 : f.n <= 8192 ? 2 : f.n <= 16384 ? 3 : 4;
   const int m = by_terms[f.dipole][!f.contact ? 0 : f.hm ? 2 : 1][band];
-  return f.dipole && !f.contact && band == 3 && !f.mixed ? 0 : m;
+  if (f.mixed || !f.dipole || f.hm) return m;
+  return f.contact && band == 1 ? 512 : !f.contact && band == 3 ? 0 : m;
 }
 // k_steps takes every system of members it can hold (also 4,000 of 16 with dipoles: 95
 // us as two launches, 52), but with neither dipoles nor contact the two launches' time

@@ -42,7 +42,7 @@ PER_MEMBER = 8 * 8 + 4 + 4 * 3 + 4 + 8 * 9 + 8 * 9  # tables and sums of a rod t
     (256, 16, "hm", True, True), (16, 512, "hm", False, False), (256, 64, "hm", False, False),
     (32, 200, "dipole", True, True), (4, 1024, "dipole", True, True), (3, 1025, "dipole", False, False),
     (128, 96, "dipole", False, True), (100, 200, "dipole", False, False),
-    (4, 1024, "dipole+contact", True, True), (16, 512, "dipole+contact", False, False),
+    (4, 1024, "dipole+contact", False, True), (8, 512, "dipole+contact", True, True), (16, 512, "dipole+contact", False, False),
     (400, 64, "dipole+contact", True, True), (400, 20, "dipole+contact", False, False),
     (16, 512, "dipole+hm", False, False), (400, 64, "dipole+hm", True, True),
     (511, 64, "dipole+hm", True, True), (512, 64, "dipole+hm", False, False),
