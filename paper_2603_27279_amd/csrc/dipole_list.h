@@ -60,7 +60,10 @@ __device__ __forceinline__ unsigned dl_bucket(const Dev& d, int gx, int gy, int 
 }
 
 // Bucket and counting slot of particle i (`valid`: it exists; whole waves call), and
-// its share of its block of buckets, one addition per wave and block.
+// its share of its block of buckets, one addition per wave and block. The blocks are few,
+// so workgroups add to one of DL_COPIES sets of sums: 87,000 particles in an evaluation
+// 57 us on one set, 18 on eight and 13 on 16 as on 64, whose sums k_dl_start then reads
+// in 11 us against 6. The evaluation whole: 285 us on one, 243 on 16 (262,144: 589, 452).
 __device__ __forceinline__ void dl_bin(const Dev& d, long i, bool valid) {
   unsigned b = 0;
   if (valid) {
@@ -75,7 +78,8 @@ __device__ __forceinline__ void dl_bin(const Dev& d, long i, bool valid) {
   while (todo != 0ull) {
     const int lead = __ffsll((long long)todo) - 1;
     const unsigned long long same = __ballot(valid && blk == __builtin_amdgcn_readlane(blk, lead));
-    if ((int)__lane_id() == lead) atomicAdd(&d.dl_aux[blk], __popcll(same));
+    if ((int)__lane_id() == lead)
+      atomicAdd(&d.dl_aux[(long)(blockIdx.x % DL_COPIES) * (d.dl_nb / DL_SCAN) + blk], __popcll(same));
     todo &= ~same;
   }
 }

@@ -95,7 +95,9 @@ __global__ __launch_bounds__(256) void k_dl_start(Dev d, int build) {
   __shared__ int sh[256];
   const int t = threadIdx.x;
   int off = 0;
-  for (int k = t; k < (int)blockIdx.x; k += 256) off += d.dl_aux[k];
+  for (int k = t; k < (int)blockIdx.x; k += 256)
+#pragma unroll
+    for (int c = 0; c < DL_COPIES; ++c) off += d.dl_aux[(long)c * (d.dl_nb / DL_SCAN) + k];
   off = dl_block_sum(off, sh);
   int* c = d.dl_cnt + (long)blockIdx.x * DL_SCAN + 8 * t;
   int v[8], s = 0;
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(256) void k_dl_scatter(Dev d, int build) {
 __global__ __launch_bounds__(256) void k_dl_rank(Dev d, int build) {
   if (!lists_stale(d, build)) return;
   const long G = (long)gridDim.x * blockDim.x, first = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  for (long k = first; k < d.dl_nb / DL_SCAN; k += G)
+  for (long k = first; k < DL_COPIES * (long)(d.dl_nb / DL_SCAN); k += G)
     d.dl_aux[k] = 0;  // (its sums have been used) for the next rebuild
   for (long i = first; i < d.n; i += G) {
     const int b = d.dl_bkt[i];

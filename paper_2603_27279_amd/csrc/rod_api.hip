@@ -763,7 +763,7 @@ static size_t workspace_bytes(const rod_desc* d, int max_slots) {
   if (dcut) b += (4 * DNBR_CAP + 4 + 64) * N;                                   // dipole lists
   if (dcut) {                                                                   // cutoff sort
     const DlGeo g = dl_geometry(d);
-    b += 4 * (2 * (size_t)g.nb + 1 + g.nb / DL_SCAN) + (4 * 5 + sizeof(DlRec)) * N;
+    b += 4 * (2 * (size_t)g.nb + 1 + DL_COPIES * (g.nb / DL_SCAN)) + (4 * 5 + sizeof(DlRec)) * N;
   }
   if ((long)N >= CONTACT_LANES_MAX_N || dcut) b += 320 * ((N + BK_OWN - 1) / BK_OWN);  // block ends
   if (hm) b += (24 + 8 + 2 * HM_CAP * (4 + 24)) * N;                            // torque, contacts
@@ -1298,7 +1298,7 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
     }
     d.dl_mshift = g.mshift;
     d.dl_nb = g.nb;
-    if ((rc = dalloc(c, &d.dl_cnt, (size_t)g.nb)) || (rc = dalloc(c, &d.dl_aux, (size_t)g.nb / DL_SCAN)) ||
+    if ((rc = dalloc(c, &d.dl_cnt, (size_t)g.nb)) || (rc = dalloc(c, &d.dl_aux, DL_COPIES * ((size_t)g.nb / DL_SCAN))) ||
         (rc = dalloc(c, &d.dl_start, (size_t)g.nb + 1)) || (rc = dalloc(c, &d.dl_bkt, (size_t)N)) ||
         (rc = dalloc(c, &d.dl_slot, (size_t)N)) || (rc = dalloc(c, &d.dl_tmp, (size_t)N)) ||
         (rc = dalloc(c, &d.dl_sorted, (size_t)N)) || (rc = dalloc(c, &d.dl_pos, (size_t)N)) ||

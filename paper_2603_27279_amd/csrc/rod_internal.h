@@ -147,7 +147,8 @@ struct Dev {
   int dl_mshift;
   int dl_nb;               // buckets (a power of two, a multiple of DL_SCAN)
   int* dl_cnt;             // [nb] particles per bucket (zero between rebuilds)
-  int* dl_aux;             // [nb / DL_SCAN] particles per block of buckets (zero between rebuilds)
+  int* dl_aux;             // [DL_COPIES][nb / DL_SCAN] particles per block of buckets, added up by the
+                           // workgroups in turn (zero between rebuilds)
   int* dl_start;           // [nb + 1] first sorted position of each bucket
   int* dl_bkt;             // [N] bucket of each particle
   int* dl_slot;            // [N] its counting slot in the bucket
@@ -219,6 +220,7 @@ constexpr double NBR_MOVE = 0.45;               // rebuild past this fraction of
 constexpr int HM_CAP = 32;                      // Hertz-Mindlin contacts kept per particle
 constexpr int DNBR_CAP = 256;                   // dipole list entries per particle (cutoff)
 constexpr int DL_SCAN = 2048;                   // buckets per block of the cutoff sort's sums
+constexpr int DL_COPIES = 16;                   // of those sums (dl_bin)
 enum { FLAG_NONFINITE = 0, FLAG_DIP_OVF = 1, FLAG_LIST_OVF = 2, FLAG_HM_OVF = 3,
        FLAG_CONTACT_RANGE = 4, FLAG_COUNT = 5 };
 // Exponent that maps a pair-term bound b to 2^80 in the exact contact sums.
