@@ -1298,7 +1298,8 @@ int rod_init(rod_ctx** out, const rod_desc* dsc, const rod_buffers* b, void* hip
     }
     d.dl_mshift = g.mshift;
     d.dl_nb = g.nb;
-    if ((rc = dalloc(c, &d.dl_cnt, (size_t)g.nb)) || (rc = dalloc(c, &d.dl_aux, DL_COPIES * ((size_t)g.nb / DL_SCAN))) ||
+    if ((rc = dalloc(c, &d.dl_cnt, (size_t)g.nb)) ||
+        (rc = dalloc(c, &d.dl_aux, DL_COPIES * ((size_t)g.nb / DL_SCAN))) ||
         (rc = dalloc(c, &d.dl_start, (size_t)g.nb + 1)) || (rc = dalloc(c, &d.dl_bkt, (size_t)N)) ||
         (rc = dalloc(c, &d.dl_slot, (size_t)N)) || (rc = dalloc(c, &d.dl_tmp, (size_t)N)) ||
         (rc = dalloc(c, &d.dl_sorted, (size_t)N)) || (rc = dalloc(c, &d.dl_pos, (size_t)N)) ||
